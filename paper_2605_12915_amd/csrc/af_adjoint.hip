@@ -257,30 +257,7 @@ __global__ void __launch_bounds__(kFNT, 2) k_adj_fwd(StatePtrs<double> prim, dou
     if (own) {
         const IntAcc<kFBX, kFBY> A{&L};
         const PolAbs<double> pol{gamma, 1.0 / (gamma - 1.0)};
-        double d[2][3];
-        node_increments<F_V>(A, ox, oy, pol, lam0, lam1, d, st);
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int v = 0; v < 3; ++v) D[(size_t)(t * 12 + 0 * 3 + v) * N + g] = d[t][v];
-        __builtin_amdgcn_sched_barrier(0);   // one family at a time: interleaving them spills
-        node_increments<F_EV>(A, ox, oy, pol, lam0, lam1, d, st);
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int v = 0; v < 3; ++v) D[(size_t)(t * 12 + 1 * 3 + v) * N + g] = d[t][v];
-        __builtin_amdgcn_sched_barrier(0);
-        node_increments<F_EH>(A, ox, oy, pol, lam0, lam1, d, st);
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int v = 0; v < 3; ++v) D[(size_t)(t * 12 + 2 * 3 + v) * N + g] = d[t][v];
-        __builtin_amdgcn_sched_barrier(0);
-        node_increments<F_C>(A, ox, oy, pol, lam0, lam1, d, st);
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int v = 0; v < 3; ++v) D[(size_t)(t * 12 + 3 * 3 + v) * N + g] = d[t][v];
+        cell_increments(A, ox, oy, pol, lam0, lam1, st, [&](int pl, double v) { D[(size_t)pl * N + g] = v; });
     }
     if (st) atomicOr(status, st);
 }

@@ -11,6 +11,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <utility>
+
 #include "af_blocks.h"
 #include "af_internal.h"
 
@@ -184,6 +186,100 @@ AF_HD void node_increment(const NodeAcc<T>& A, T r, T Z, T iZ, T inc[3]) {
     inc[0] = r * (s[2] * iZ + s[3]);
     inc[1] = r * (s[4] * iZ + s[5]);
     inc[2] = r * (s[0] + Z * s[1]);
+}
+
+// The same operator in folded form.  The wedges of a node are mirror images of one
+// another, and so are their blocks (a factor -1 per odd power and per odd channel), so
+// the sum over them needs the data only in even and odd parts: along a line of five
+// nodes f at X = -1, -1/2, 0, 1/2, 1 about the node the monomial coefficients in |X| of
+// f(X) + f(-X) and f(X) - f(-X), along a line of three nodes at X = -1/2, 0, 1/2 (one
+// cell) the coefficients in X.  Each block entry is then applied once per node instead of
+// once per wedge, and lines along x are shared by the nodes above one another.
+// Coefficients are stored without a factor 2 that the block constants take (LineTerm).
+struct LineTerm { int pow; bool odd; double scale; };
+template <int N> struct LineTerms;
+template <> struct LineTerms<5> {
+    static constexpr LineTerm t[5] = {{0, false, 2.0}, {1, false, 1.0}, {2, false, 2.0}, {1, true, 1.0}, {2, true, 2.0}};
+};
+template <> struct LineTerms<3> {
+    static constexpr LineTerm t[3] = {{0, false, 1.0}, {1, true, 1.0}, {2, false, 2.0}};
+};
+
+// Line transform, in differences so that constants give exact zeros.  DIFF: differences
+// from the middle node first (node values); otherwise fewer operations (for values that
+// are differences along the other direction already).
+template <int N, bool DIFF, class T>
+AF_HD void line(const T* f, T* c) {
+    if constexpr (N == 5) {
+        T e1, e2;
+        const T o1 = f[3] - f[1], o2 = f[4] - f[0];
+        if constexpr (DIFF) {
+            e1 = (f[3] - f[2]) + (f[1] - f[2]);
+            e2 = (f[4] - f[2]) + (f[0] - f[2]);
+        } else {
+            e1 = (f[3] + f[1]) - T(2) * f[2];
+            e2 = (f[4] + f[0]) - T(2) * f[2];
+        }
+        c[0] = f[2];
+        c[1] = T(4) * e1 - e2;
+        c[2] = e2 - T(2) * e1;
+        c[3] = T(4) * o1 - o2;
+        c[4] = o2 - T(2) * o1;
+    } else {
+        c[0] = f[1];
+        c[1] = f[2] - f[0];
+        c[2] = (f[2] - f[1]) + (f[0] - f[1]);
+    }
+}
+
+// acc[out][m] += the r^(m+1) coefficient of channel out (0: pi, 1: u, 2: v) from the
+// line coefficients c of variable VAR (0: pi, 1: u, 2: v); W: the node's wedge with X, Y > 0.
+template <int W, int NX, int NY, int VAR, int A, int B, int OUT, class T>
+AF_HD void block_term(const T (&c)[NX][NY], T (&acc)[3][4]) {
+    constexpr LineTerm x = LineTerms<NX>::t[A], y = LineTerms<NY>::t[B];
+    // odd in x where exactly one of the two is u, odd in y where one is v
+    constexpr bool match = x.odd == ((OUT == 1) != (VAR == 1)) && y.odd == ((OUT == 2) != (VAR == 2));
+    if constexpr (match && x.pow + y.pow > 0) {
+        constexpr double w = kBlk[W][x.pow][y.pow][3 * OUT + VAR] * x.scale * y.scale;
+        if constexpr (w != 0.0) acc[OUT][x.pow + y.pow - 1] += T(w) * c[A][B];
+    }
+}
+
+template <int W, int NX, int NY, int VAR, class T, int... K>
+AF_HD void block_terms(const T (&c)[NX][NY], T (&acc)[3][4], std::integer_sequence<int, K...>) {
+    (block_term<W, NX, NY, VAR, K / (3 * NY), (K / 3) % NY, K % 3>(c, acc), ...);
+}
+
+template <int W, int NX, int NY, int VAR, class T>
+AF_HD void block_acc(const T (&c)[NX][NY], T (&acc)[3][4]) {
+    block_terms<W, NX, NY, VAR>(c, acc, std::make_integer_sequence<int, 3 * NX * NY>());
+}
+
+template <class T>
+AF_HD void zero_acc(T (&acc)[3][4]) {
+#pragma unroll
+    for (int o = 0; o < 3; ++o)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) acc[o][m] = T(0);
+}
+
+template <class T>
+AF_HD void scale_acc(T (&acc)[3][4], T s) {
+#pragma unroll
+    for (int o = 0; o < 3; ++o)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) acc[o][m] = acc[o][m] * s;
+}
+
+// Increments (du, dv, dp) at radius r from the sums (pressure channel as p / Z).
+template <class T>
+AF_HD void block_increment(const T a[3][4], T r, T Z, T inc[3]) {
+    T s[3];
+#pragma unroll
+    for (int o = 0; o < 3; ++o) s[o] = ((a[o][3] * r + a[o][2]) * r + a[o][1]) * r + a[o][0];
+    inc[0] = r * s[1];
+    inc[1] = r * s[2];
+    inc[2] = (r * Z) * s[0];
 }
 
 // ---------------------------------------------------------------------------

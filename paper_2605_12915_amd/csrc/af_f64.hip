@@ -80,20 +80,8 @@ __global__ void __launch_bounds__(256) k_incr(StatePtrs<double> in, const double
 #pragma unroll
     for (int k = 0; k < 16; ++k) A.s[k] = in.p[k];
     unsigned st = 0;
-    double d[2][3];
     const size_t N = (size_t)nx * ny, c = (size_t)j * nx + i;
-    node_increments<F_V>(A, i, j, pol, lam0, lam1, d, st);
-    for (int t = 0; t < 2; ++t)
-        for (int v = 0; v < 3; ++v) inc[(size_t)(t * 12 + 0 * 3 + v) * N + c] = d[t][v];
-    node_increments<F_EV>(A, i, j, pol, lam0, lam1, d, st);
-    for (int t = 0; t < 2; ++t)
-        for (int v = 0; v < 3; ++v) inc[(size_t)(t * 12 + 1 * 3 + v) * N + c] = d[t][v];
-    node_increments<F_EH>(A, i, j, pol, lam0, lam1, d, st);
-    for (int t = 0; t < 2; ++t)
-        for (int v = 0; v < 3; ++v) inc[(size_t)(t * 12 + 2 * 3 + v) * N + c] = d[t][v];
-    node_increments<F_C>(A, i, j, pol, lam0, lam1, d, st);
-    for (int t = 0; t < 2; ++t)
-        for (int v = 0; v < 3; ++v) inc[(size_t)(t * 12 + 3 * 3 + v) * N + c] = d[t][v];
+    cell_increments(A, i, j, pol, lam0, lam1, st, [&](int pl, double v) { inc[(size_t)pl * N + c] = v; });
     if (st) atomicOr(status, st);
 }
 

@@ -23,11 +23,6 @@ __device__ __forceinline__ void store_prim(const SP& o, size_t g, const Prim<T>&
 // tiles of many grids per workgroup).  The arithmetic of every node does not depend
 // on the tile shape or on which kernel calls it; compiled with -ffp-contract=on in
 // both, the FP32 kernels therefore agree bit for bit.
-// Phase 2 computes the four families' increments one after the other with a
-// scheduling fence between them.  Interleaving them (the compiler's choice without it)
-// needs more registers than a wave holds at these occupancies and spills: in FP64
-// beyond 256, in the FP32 kernels (128 at two workgroups per CU) 14 registers, whose
-// scratch traffic reached HBM (1.9x the algorithmic bytes written).
 //
 // SP: any type with a member p such that p[k] is plane k's pointer (StatePtrs, or a
 // view of a descriptor in global memory whose pointers are loaded where used).
@@ -111,30 +106,8 @@ __device__ __forceinline__ void fused_tile(FusedTile<T, TX, TY>& L, const SP& in
         for (int e = tid; e < Tile::SD * Tile::DY; e += NT) {
             int x, y;
             if (!Tile::incr_item(e, x, y)) continue;
-            T d[2][3];
-            node_increments<F_V>(A, x, y, pol, lam0, lam1, d, st);
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int v = 0; v < 3; ++v) L.D[t][0 * 3 + v][y + 1][x + 1] = d[t][v];
-            __builtin_amdgcn_sched_barrier(0);   // one family at a time
-            node_increments<F_EV>(A, x, y, pol, lam0, lam1, d, st);
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int v = 0; v < 3; ++v) L.D[t][1 * 3 + v][y + 1][x + 1] = d[t][v];
-            __builtin_amdgcn_sched_barrier(0);   // one family at a time
-            node_increments<F_EH>(A, x, y, pol, lam0, lam1, d, st);
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int v = 0; v < 3; ++v) L.D[t][2 * 3 + v][y + 1][x + 1] = d[t][v];
-            __builtin_amdgcn_sched_barrier(0);   // one family at a time
-            node_increments<F_C>(A, x, y, pol, lam0, lam1, d, st);
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int v = 0; v < 3; ++v) L.D[t][3 * 3 + v][y + 1][x + 1] = d[t][v];
+            cell_increments(A, x, y, pol, lam0, lam1, st,
+                            [&](int pl, T v) { L.D[pl / 12][pl % 12][y + 1][x + 1] = v; });
         }
     }
     __syncthreads();

@@ -103,27 +103,7 @@ __global__ void __launch_bounds__(NT) k_acoustic(StatePtrs<double> in, double* C
         const int x = e % TX, y = e / TX;
         if (i0 + x >= nx || j0 + y >= ny) continue;
         const size_t g = (size_t)(j0 + y) * nx + (i0 + x);
-        double d[2][3];
-        node_increments<F_V>(A, x, y, pol, lam0, lam1, d, st);
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int v = 0; v < 3; ++v) Dout[(size_t)(t * 12 + 0 + v) * N + g] = d[t][v];
-        node_increments<F_EV>(A, x, y, pol, lam0, lam1, d, st);
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int v = 0; v < 3; ++v) Dout[(size_t)(t * 12 + 3 + v) * N + g] = d[t][v];
-        node_increments<F_EH>(A, x, y, pol, lam0, lam1, d, st);
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int v = 0; v < 3; ++v) Dout[(size_t)(t * 12 + 6 + v) * N + g] = d[t][v];
-        node_increments<F_C>(A, x, y, pol, lam0, lam1, d, st);
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int v = 0; v < 3; ++v) Dout[(size_t)(t * 12 + 9 + v) * N + g] = d[t][v];
+        cell_increments(A, x, y, pol, lam0, lam1, st, [&](int pl, double v) { Dout[(size_t)pl * N + g] = v; });
     }
     if (st) atomicOr(status, st);
 }

@@ -117,15 +117,18 @@ int main() {
     long centre = total() - c0;
     c0 = total();
     Cnt d[2][3];
+    // a pair of families shares its lines along x: V and C are counted alone (outside the
+    // totals), Ev and Eh as what they add to V's and C's pairs
+    const long keep[4] = {g_add, g_mul, g_div, g_sqrt};
     node_increments<F_V>(A, 2, 2, pol, lam0, lam1, d, st);
-    long incV = total() - c0;
-    c0 = total();
-    node_increments<F_EV>(A, 2, 2, pol, lam0, lam1, d, st);
-    node_increments<F_EH>(A, 2, 2, pol, lam0, lam1, d, st);
-    long incE = total() - c0;
+    const long incV = total() - c0;
     c0 = total();
     node_increments<F_C>(A, 2, 2, pol, lam0, lam1, d, st);
-    long incC = total() - c0;
+    const long incC = total() - c0;
+    g_add = keep[0]; g_mul = keep[1]; g_div = keep[2]; g_sqrt = keep[3];
+    c0 = total();
+    cell_increments(A, 2, 2, pol, lam0, lam1, st, [](int, Cnt) {});
+    const long incE = total() - c0 - incV - incC;
     c0 = total();
     Prim<Cnt> w[3][2];
     w[0][0] = point_update<F_V, 0>(A, D, 2, 2, pol, lam0, st);
@@ -184,10 +187,7 @@ int main() {
     // forward intermediates (centre of the cell, increments of its four nodes)
     recover_centre(Ub, A.node(F_V, 2, 2), A.node(F_V, 3, 2), A.node(F_V, 2, 3), A.node(F_V, 3, 3),
                    A.node(F_EH, 2, 2), A.node(F_EH, 2, 3), A.node(F_EV, 2, 2), A.node(F_EV, 3, 2), gamma);
-    node_increments<F_V>(A, 2, 2, pol, lam0, lam1, d, st);
-    node_increments<F_EV>(A, 2, 2, pol, lam0, lam1, d, st);
-    node_increments<F_EH>(A, 2, 2, pol, lam0, lam1, d, st);
-    node_increments<F_C>(A, 2, 2, pol, lam0, lam1, d, st);
+    cell_increments(A, 2, 2, pol, lam0, lam1, st, [](int, Cnt) {});
     const long adj_fwd = total() - a0;
     long a1 = total();
     unsigned fix = point_adj_target<F_V, 0, 0>(S, cot, O, 2, 2, gamma, lam0, lam1);
