@@ -233,26 +233,27 @@ AF_HD void line(const T* f, T* c) {
 }
 
 // acc[out][m] += the r^(m+1) coefficient of channel out (0: pi, 1: u, 2: v) from the
-// line coefficients c of variable VAR (0: pi, 1: u, 2: v); W: the node's wedge with X, Y > 0.
+// coefficients c along y of variable VAR's (0: pi, 1: u, 2: v) coefficient A along x; W:
+// the node's wedge with X, Y > 0.
 template <int W, int NX, int NY, int VAR, int A, int B, int OUT, class T>
-AF_HD void block_term(const T (&c)[NX][NY], T (&acc)[3][4]) {
+AF_HD void block_term(const T (&c)[NY], T (&acc)[3][4]) {
     constexpr LineTerm x = LineTerms<NX>::t[A], y = LineTerms<NY>::t[B];
     // odd in x where exactly one of the two is u, odd in y where one is v
     constexpr bool match = x.odd == ((OUT == 1) != (VAR == 1)) && y.odd == ((OUT == 2) != (VAR == 2));
     if constexpr (match && x.pow + y.pow > 0) {
         constexpr double w = kBlk[W][x.pow][y.pow][3 * OUT + VAR] * x.scale * y.scale;
-        if constexpr (w != 0.0) acc[OUT][x.pow + y.pow - 1] += T(w) * c[A][B];
+        if constexpr (w != 0.0) acc[OUT][x.pow + y.pow - 1] += T(w) * c[B];
     }
 }
 
-template <int W, int NX, int NY, int VAR, class T, int... K>
-AF_HD void block_terms(const T (&c)[NX][NY], T (&acc)[3][4], std::integer_sequence<int, K...>) {
-    (block_term<W, NX, NY, VAR, K / (3 * NY), (K / 3) % NY, K % 3>(c, acc), ...);
+template <int W, int NX, int NY, int VAR, int A, class T, int... K>
+AF_HD void block_terms(const T (&c)[NY], T (&acc)[3][4], std::integer_sequence<int, K...>) {
+    (block_term<W, NX, NY, VAR, A, K / 3, K % 3>(c, acc), ...);
 }
 
-template <int W, int NX, int NY, int VAR, class T>
-AF_HD void block_acc(const T (&c)[NX][NY], T (&acc)[3][4]) {
-    block_terms<W, NX, NY, VAR>(c, acc, std::make_integer_sequence<int, 3 * NX * NY>());
+template <int W, int NX, int NY, int VAR, int A, class T>
+AF_HD void block_acc(const T (&c)[NY], T (&acc)[3][4]) {
+    block_terms<W, NX, NY, VAR, A>(c, acc, std::make_integer_sequence<int, 3 * NY>());
 }
 
 template <class T>
@@ -271,15 +272,15 @@ AF_HD void scale_acc(T (&acc)[3][4], T s) {
         for (int m = 0; m < 4; ++m) acc[o][m] = acc[o][m] * s;
 }
 
-// Increments (du, dv, dp) at radius r from the sums (pressure channel as p / Z).
+// Increments (du, dv, dp) at radius r from the sums (channels in units of p).
 template <class T>
-AF_HD void block_increment(const T a[3][4], T r, T Z, T inc[3]) {
+AF_HD void block_increment(const T a[3][4], T r, T iZ, T inc[3]) {
     T s[3];
 #pragma unroll
     for (int o = 0; o < 3; ++o) s[o] = ((a[o][3] * r + a[o][2]) * r + a[o][1]) * r + a[o][0];
-    inc[0] = r * s[1];
-    inc[1] = r * s[2];
-    inc[2] = (r * Z) * s[0];
+    inc[0] = (r * iZ) * s[1];
+    inc[1] = (r * iZ) * s[2];
+    inc[2] = r * s[0];
 }
 
 // ---------------------------------------------------------------------------

@@ -101,13 +101,28 @@ __device__ __forceinline__ void fused_tile(FusedTile<T, TX, TY>& L, const SP& in
     __syncthreads();
 
     // ---- phase 2: increments at node-cells [-1, T+2)^2, both durations ---------------
+    // (transported update: the velocities' planes hold u + du and v + dv)
+    constexpr bool kSum = SCHEME == 0;
     {
         LdsAcc<T, TX, TY> A{&L};
-        for (int e = tid; e < Tile::SD * Tile::DY; e += NT) {
-            int x, y;
-            if (!Tile::incr_item(e, x, y)) continue;
-            cell_increments(A, x, y, pol, lam0, lam1, st,
-                            [&](int pl, T v) { L.D[pl / 12][pl % 12][y + 1][x + 1] = v; });
+        constexpr int NI = (Tile::SD * Tile::DY + 63) / 64 * 64;   // items of one pair, in whole wavefronts
+        int x, y;
+        auto put = [&](int pl, T v) {
+            const int fam = (pl % 12) / 3, q = pl % 3;
+            if (kSum && q == 0) v = A.node(fam, x, y).u + v;
+            if (kSum && q == 1) v = A.node(fam, x, y).v + v;
+            L.D[pl / 12][pl % 12][y + 1][x + 1] = v;
+        };
+        if constexpr (NT >= 2 * NI) {
+            // threads enough for both pairs of families at once, one pair per wavefront
+            if (tid < NI) {
+                if (Tile::incr_item(tid, x, y)) put_pair<5>(A, x, y, pol, lam0, lam1, st, put);
+            } else if (tid < 2 * NI) {
+                if (Tile::incr_item(tid - NI, x, y)) put_pair<3>(A, x, y, pol, lam0, lam1, st, put);
+            }
+        } else {
+            for (int e = tid; e < Tile::SD * Tile::DY; e += NT)
+                if (Tile::incr_item(e, x, y)) cell_increments(A, x, y, pol, lam0, lam1, st, put);
         }
     }
     __syncthreads();
@@ -133,7 +148,7 @@ __device__ __forceinline__ void fused_tile(FusedTile<T, TX, TY>& L, const SP& in
             const size_t g = own ? (size_t)(j0 + y) * nx + (i0 + x) : 0;
             if constexpr (DYN) {
                 w0 = A.node(fam, x, y);
-                point_update_pair_f<SCHEME>(A, D0, D1, fam, x, y, pol, lam0, lam1, st, wh, w1);
+                point_update_pair_f<SCHEME, kSum>(A, D0, D1, fam, x, y, pol, lam0, lam1, st, wh, w1);
                 if (own) {
                     if (fam == F_V) store_prim<4>(out, g, w1);
                     else if (fam == F_EV) store_prim<8>(out, g, w1);
@@ -141,15 +156,15 @@ __device__ __forceinline__ void fused_tile(FusedTile<T, TX, TY>& L, const SP& in
                 }
             } else if (fam == F_V) {
                 w0 = A.node(F_V, x, y);
-                point_update_pair<F_V, SCHEME>(A, D0, D1, x, y, pol, lam0, lam1, st, wh, w1);
+                point_update_pair<F_V, SCHEME, kSum>(A, D0, D1, x, y, pol, lam0, lam1, st, wh, w1);
                 if (own) store_prim<4>(out, g, w1);
             } else if (fam == F_EV) {
                 w0 = A.node(F_EV, x, y);
-                point_update_pair<F_EV, SCHEME>(A, D0, D1, x, y, pol, lam0, lam1, st, wh, w1);
+                point_update_pair<F_EV, SCHEME, kSum>(A, D0, D1, x, y, pol, lam0, lam1, st, wh, w1);
                 if (own) store_prim<8>(out, g, w1);
             } else {
                 w0 = A.node(F_EH, x, y);
-                point_update_pair<F_EH, SCHEME>(A, D0, D1, x, y, pol, lam0, lam1, st, wh, w1);
+                point_update_pair<F_EH, SCHEME, kSum>(A, D0, D1, x, y, pol, lam0, lam1, st, wh, w1);
                 if (own) store_prim<12>(out, g, w1);
             }
             T F0[4], Fh[4], F1[4];

@@ -56,42 +56,97 @@ AF_HD void node_wedges(const A& acc, int i, int j, NodeAcc<T>& na) {
     }
 }
 
-// Node freezing (Sec. 6.1 step 1): c_K, Z_K and 1 / Z_K, and the radii r_k = c_K lam_k
-// for two durations tau_k = lam_k h (k = 0: dt/2, 1: dt).  Sets SB_CFL if
-// c_K dt / h > 1/2 and SB_NONPHYS if the node state is not physical.
+// Node freezing (Sec. 6.1 step 1): c_K, Z_K and 1 / Z_K.  Sets SB_CFL if c_K dt / h > 1/2
+// (lam1 = dt / h) and SB_NONPHYS if the node state is not physical.
 template <class T>
-struct Freeze { T Z, iZ, r0, r1; };
+struct Freeze { T c, Z, iZ; };
 
 template <class T, class Pol>
-AF_HD Freeze<T> freeze_node(const Prim<T>& Wn, const Pol& pol, T lam0, T lam1, unsigned& st) {
+AF_HD Freeze<T> freeze_node(const Prim<T>& Wn, const Pol& pol, T lam1, unsigned& st) {
     const T rK = pol.rho(Wn.r), pK = pol.pr(Wn.p);
     if (!(rK > T(0)) || !(pK > T(0))) st |= SB_NONPHYS;
     // c = sqrt(gamma p / rho) and Z = rho c from one reciprocal square root:
     // 1 / Z = (gamma p rho)^(-1/2), c = gamma p / Z, Z = gamma p rho / Z
     const T gp = pol.gamma * pK, q = gp * rK;
     const T iZ = rsqrt_of(q);
-    const T c = gp * iZ;
-    const Freeze<T> z{q * iZ, iZ, c * lam0, c * lam1};
-    if (!(z.r1 <= T(0.5))) st |= SB_CFL;
+    const Freeze<T> z{gp * iZ, q * iZ, iZ};
+    if (!(z.c * lam1 <= T(0.5))) st |= SB_CFL;
     return z;
 }
 
-// Variable VAR (0: p, 1: u, 2: v) at (a, b) half cells from the vertex of cell (i, j).
+// Fence between stages whose live values together exceed a wave's registers: the sums so
+// far are complete here (pinned to registers), and nothing moves across.
+template <class T>
+AF_HD void pin(T& x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(x));
+#endif
+}
+
+template <class T>
+AF_HD void stage_fence(T (&a1)[3][4], T (&a2)[3][4]) {
+#pragma unroll
+    for (int o = 0; o < 3; ++o)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) { pin(a1[o][m]); pin(a2[o][m]); }
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_sched_barrier(0);
+#endif
+}
+
+// Variable VAR (0: p, 1: u, 2: v, 3: rho) at (a, b) half cells from the vertex of cell (i, j).
 template <int VAR, class T, class A>
 AF_HD T lattice(const A& acc, int i, int j, int a, int b) {
     const int fam = (a & 1) ? ((b & 1) ? F_C : F_EH) : ((b & 1) ? F_EV : F_V);
     const Prim<T> n = acc.node(fam, i + (a - (a & 1)) / 2, j + (b - (b & 1)) / 2);
-    return VAR == 0 ? n.p : (VAR == 1 ? n.u : n.v);
+    return VAR == 0 ? n.p : (VAR == 1 ? n.u : (VAR == 2 ? n.v : n.r));
+}
+
+// The nine nodal values [x-node][y-node] of one variable (0: p, 1: u, 2: v, 3: rho) of
+// cell (ci, cj), and those of one increment.
+template <int VAR, class T, class A>
+AF_HD void cell_field(const A& acc, int ci, int cj, T f[3][3]) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) f[a][b] = lattice<VAR, T>(acc, ci, cj, a, b);
+}
+
+template <class T, class D>
+AF_HD void cell_inc(const D& dinc, int ci, int cj, int var, T g[3][3]) {
+    g[0][0] = dinc.inc(F_V, ci, cj, var);      g[1][0] = dinc.inc(F_EH, ci, cj, var);
+    g[2][0] = dinc.inc(F_V, ci + 1, cj, var);  g[0][1] = dinc.inc(F_EV, ci, cj, var);
+    g[1][1] = dinc.inc(F_C, ci, cj, var);      g[2][1] = dinc.inc(F_EV, ci + 1, cj, var);
+    g[0][2] = dinc.inc(F_V, ci, cj + 1, var);  g[1][2] = dinc.inc(F_EH, ci, cj + 1, var);
+    g[2][2] = dinc.inc(F_V, ci + 1, cj + 1, var);
+}
+
+// One coefficient along x (A) of every row, taken along y for both nodes of a pair.
+template <int NX, bool FIRST, bool SECOND, int VAR, int A, class T>
+AF_HD void pair_column(const T (&row)[5][NX], T (&a1)[3][4], T (&a2)[3][4]) {
+    constexpr int W1 = NX == 5 ? W_V_NE : W_EH_U, W2 = NX == 5 ? W_EV_R : W_C;
+    if constexpr (FIRST) {
+        const T f[5] = {row[0][A], row[1][A], row[2][A], row[3][A], row[4][A]};
+        T c[5];
+        line<5, A == 0>(f, c);
+        block_acc<W1, NX, 5, VAR, A>(c, a1);
+    }
+    if constexpr (SECOND) {
+        const T f[3] = {row[2][A], row[3][A], row[4][A]};
+        T c[3];
+        line<3, true>(f, c);
+        block_acc<W2, NX, 3, VAR, A>(c, a2);
+    }
 }
 
 // Block sums of one variable for a pair of node families that read the same lines of
 // nodes along x: NX = 5, the vertex (i, j) (first, full reach in y) and the vertical-edge
 // midpoint (i, j + 1/2) (second, rows j .. j + 1) over x in [i - 1, i + 1]; NX = 3, the
 // horizontal-edge midpoint (i + 1/2, j) and the centre (i + 1/2, j + 1/2) over x in
-// [i, i + 1].  The pressure enters as p / Z_K of each node.
+// [i, i + 1].
 template <int NX, bool FIRST, bool SECOND, int VAR, class T, class A>
-AF_HD void pair_blocks(const A& acc, int i, int j, T iZ1, T iZ2, T (&a1)[3][4], T (&a2)[3][4]) {
-    constexpr int W1 = NX == 5 ? W_V_NE : W_EH_U, W2 = NX == 5 ? W_EV_R : W_C, X0 = NX == 5 ? -2 : 0;
+AF_HD void pair_blocks(const A& acc, int i, int j, T (&a1)[3][4], T (&a2)[3][4]) {
+    constexpr int X0 = NX == 5 ? -2 : 0;
     T row[5][NX];
 #pragma unroll
     for (int b = FIRST ? 0 : 2; b < 5; ++b) {
@@ -100,80 +155,79 @@ AF_HD void pair_blocks(const A& acc, int i, int j, T iZ1, T iZ2, T (&a1)[3][4], 
         for (int a = 0; a < NX; ++a) f[a] = lattice<VAR, T>(acc, i, j, X0 + a, b - 2);
         line<NX, true>(f, row[b]);
     }
-    if constexpr (FIRST) {
-        T c[NX][5];
-#pragma unroll
-        for (int a = 0; a < NX; ++a) {
-            const T f[5] = {row[0][a], row[1][a], row[2][a], row[3][a], row[4][a]};
-            if (a == 0) line<5, true>(f, c[a]);
-            else line<5, false>(f, c[a]);
-        }
-        block_acc<W1, NX, 5, VAR>(c, a1);
-        if constexpr (VAR == 0) scale_acc(a1, iZ1);
-    }
-    if constexpr (SECOND) {
-        T c[NX][3];
-#pragma unroll
-        for (int a = 0; a < NX; ++a) {
-            const T f[3] = {row[2][a], row[3][a], row[4][a]};
-            line<3, true>(f, c[a]);
-        }
-        block_acc<W2, NX, 3, VAR>(c, a2);
-        if constexpr (VAR == 0) scale_acc(a2, iZ2);
+    pair_column<NX, FIRST, SECOND, VAR, 0>(row, a1, a2);
+    pair_column<NX, FIRST, SECOND, VAR, 1>(row, a1, a2);
+    pair_column<NX, FIRST, SECOND, VAR, 2>(row, a1, a2);
+    if constexpr (NX == 5) {
+        pair_column<NX, FIRST, SECOND, VAR, 3>(row, a1, a2);
+        pair_column<NX, FIRST, SECOND, VAR, 4>(row, a1, a2);
     }
 }
 
 // The node increments of a pair of families (NX as above) for both durations: inc1 of
-// the first family's node, inc2 of the second's; [duration][du, dv, dp].
+// the first family's node, inc2 of the second's; [duration][du, dv, dp].  The sums are
+// formed with the velocities first, in units of p / Z, then scaled to those of p.
 template <int NX, bool FIRST = true, bool SECOND = true, class T, class A, class Pol>
 AF_HD void pair_increments(const A& acc, int i, int j, const Pol& pol, T lam0, T lam1, T inc1[2][3], T inc2[2][3],
                            unsigned& st) {
     constexpr int F1 = NX == 5 ? F_V : F_EH, F2 = NX == 5 ? F_EV : F_C;
-    Freeze<T> z1{}, z2{};
-    if constexpr (FIRST) z1 = freeze_node(acc.node(F1, i, j), pol, lam0, lam1, st);
-    if constexpr (SECOND) z2 = freeze_node(acc.node(F2, i, j), pol, lam0, lam1, st);
     T a1[3][4], a2[3][4];
     zero_acc(a1);
     zero_acc(a2);
-    pair_blocks<NX, FIRST, SECOND, 0>(acc, i, j, z1.iZ, z2.iZ, a1, a2);
-    pair_blocks<NX, FIRST, SECOND, 1>(acc, i, j, z1.iZ, z2.iZ, a1, a2);
-    pair_blocks<NX, FIRST, SECOND, 2>(acc, i, j, z1.iZ, z2.iZ, a1, a2);
+    pair_blocks<NX, FIRST, SECOND, 1>(acc, i, j, a1, a2);
+    stage_fence(a1, a2);
+    pair_blocks<NX, FIRST, SECOND, 2>(acc, i, j, a1, a2);
+    stage_fence(a1, a2);
+    Freeze<T> z1{}, z2{};
     if constexpr (FIRST) {
-        block_increment(a1, z1.r0, z1.Z, inc1[0]);
-        block_increment(a1, z1.r1, z1.Z, inc1[1]);
+        z1 = freeze_node(acc.node(F1, i, j), pol, lam1, st);
+        scale_acc(a1, z1.Z);
     }
     if constexpr (SECOND) {
-        block_increment(a2, z2.r0, z2.Z, inc2[0]);
-        block_increment(a2, z2.r1, z2.Z, inc2[1]);
+        z2 = freeze_node(acc.node(F2, i, j), pol, lam1, st);
+        scale_acc(a2, z2.Z);
+    }
+    pair_blocks<NX, FIRST, SECOND, 0>(acc, i, j, a1, a2);
+    stage_fence(a1, a2);
+    if constexpr (FIRST) {
+        block_increment(a1, z1.c * lam0, z1.iZ, inc1[0]);
+        block_increment(a1, z1.c * lam1, z1.iZ, inc1[1]);
+    }
+    if constexpr (SECOND) {
+        block_increment(a2, z2.c * lam0, z2.iZ, inc2[0]);
+        block_increment(a2, z2.c * lam1, z2.iZ, inc2[1]);
     }
 }
 
-// The increments of the four nodes of cell (i, j), put(plane, value) with plane
-// [duration][family * 3 + (du, dv, dp)].  One pair of families at a time: interleaving
-// the pairs takes more registers than a wave holds at the kernels' occupancies.  Lines
-// shared within a pair and each block entry applied once per node: 935 vector
-// instructions and 91 LDS reads per node-cell in the FP64 step kernel, against 1470 and
-// 130 with every wedge transformed on its own (FP64 step 2048^2 0.98 -> 0.86 ms, FP32
-// 4096^2 1.87 -> 1.64 ms).
+// The increments of one pair of families of cell (i, j), put(plane, value) with plane
+// [duration][family * 3 + (du, dv, dp)].
+template <int NX, class T, class A, class Pol, class Put>
+AF_HD void put_pair(const A& acc, int i, int j, const Pol& pol, T lam0, T lam1, unsigned& st, const Put& put) {
+    constexpr int F1 = NX == 5 ? F_V : F_EH, F2 = NX == 5 ? F_EV : F_C;
+    T d1[2][3], d2[2][3];
+    pair_increments<NX>(acc, i, j, pol, lam0, lam1, d1, d2, st);
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int v = 0; v < 3; ++v) {
+            put(t * 12 + F1 * 3 + v, d1[t][v]);
+            put(t * 12 + F2 * 3 + v, d2[t][v]);
+        }
+}
+
+// All four nodes of cell (i, j).  One pair of families at a time: interleaving the pairs
+// takes more registers than a wave holds at the kernels' occupancies.  Lines shared
+// within a pair and each block entry applied once per node: 935 vector instructions and
+// 91 LDS reads per node-cell in the FP64 step kernel, against 1470 and 130 with every
+// wedge transformed on its own (FP64 step 2048^2 0.98 -> 0.86 ms, FP32 4096^2 1.87 ->
+// 1.64 ms).
 template <class T, class A, class Pol, class Put>
 AF_HD void cell_increments(const A& acc, int i, int j, const Pol& pol, T lam0, T lam1, unsigned& st, const Put& put) {
-    T d1[2][3], d2[2][3];
-    auto both = [&](int f1, int f2) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int v = 0; v < 3; ++v) {
-                put(t * 12 + f1 * 3 + v, d1[t][v]);
-                put(t * 12 + f2 * 3 + v, d2[t][v]);
-            }
-    };
-    pair_increments<5>(acc, i, j, pol, lam0, lam1, d1, d2, st);
-    both(F_V, F_EV);
+    put_pair<5>(acc, i, j, pol, lam0, lam1, st, put);
 #if defined(__HIP_DEVICE_COMPILE__)
     __builtin_amdgcn_sched_barrier(0);
 #endif
-    pair_increments<3>(acc, i, j, pol, lam0, lam1, d1, d2, st);
-    both(F_EH, F_C);
+    put_pair<3>(acc, i, j, pol, lam0, lam1, st, put);
 }
 
 // One family alone (the same operations, the lines not shared).
@@ -231,14 +285,8 @@ AF_HD void picard_foot(const A& acc, int fam, int i, int j, const Pol& pol, T la
     lag_pm(xi, xm, xp);
     lag_pm(eta, ym, yp);
     T fu[3][3], fv[3][3];
-    {
-        Prim<T> n[3][3];
-        cell_nodes<T>(acc, i + cx, j + cy, n);
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) { fu[a][b] = n[a][b].u; fv[a][b] = n[a][b].v; }
-    }
+    cell_field<1>(acc, i + cx, j + cy, fu);
+    cell_field<2>(acc, i + cx, j + cy, fv);
     T u1 = q2(xm, xp, ym, yp, fu), v1 = q2(xm, xp, ym, yp, fv);
     // second Picard step from P with the velocity at the first foot
     locate(ox - lam * pol.vu(u1), ox, cx, xi, st);
@@ -247,7 +295,12 @@ AF_HD void picard_foot(const A& acc, int fam, int i, int j, const Pol& pol, T la
     cj = j + cy;
 }
 
-template <int SCHEME, class T, class A, class D, class Pol>
+//
+// SUM (SCHEME 0): the increment accessor holds u + du and v + dv in place of du and dv.
+// Interpolation is linear and both velocities are read at the same foot, so one Q2
+// evaluation of the sum gives the new velocity: five evaluations per duration at the
+// second foot instead of seven.
+template <int SCHEME, bool SUM = false, class T, class A, class D, class Pol>
 AF_HD Prim<T> point_update_f(const A& acc, const D& dinc, int fam, int i, int j, const Pol& pol, T lam,
                              unsigned& st) {
     Prim<T> WP = acc.node(fam, i, j);
@@ -256,31 +309,26 @@ AF_HD Prim<T> point_update_f(const A& acc, const D& dinc, int fam, int i, int j,
     picard_foot(acc, fam, i, j, pol, lam, WP, ci, cj, xi, eta, st);
     lag_pm(xi, xm, xp);
     lag_pm(eta, ym, yp);
-    T fr[3][3], fu[3][3], fv[3][3], fp[3][3];
-    {
-        Prim<T> n[3][3];
-        cell_nodes<T>(acc, ci, cj, n);
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                fr[a][b] = n[a][b].r; fu[a][b] = n[a][b].u; fv[a][b] = n[a][b].v; fp[a][b] = n[a][b].p;
-            }
+    T g[3][3];
+    Prim<T> Wf;
+    cell_field<3>(acc, ci, cj, g);
+    Wf.r = q2(xm, xp, ym, yp, g);
+    cell_field<0>(acc, ci, cj, g);
+    Wf.p = q2(xm, xp, ym, yp, g);
+    if constexpr (!SUM) {
+        cell_field<1>(acc, ci, cj, g);
+        Wf.u = q2(xm, xp, ym, yp, g);
+        cell_field<2>(acc, ci, cj, g);
+        Wf.v = q2(xm, xp, ym, yp, g);
     }
-    Prim<T> Wf{q2(xm, xp, ym, yp, fr), q2(xm, xp, ym, yp, fu), q2(xm, xp, ym, yp, fv), q2(xm, xp, ym, yp, fp)};
     T du, dv, dp, rho_over_c2;
     if constexpr (SCHEME == 0) {
-        T g[3][3];
-#pragma unroll
-        for (int var = 0; var < 3; ++var) {
-            g[0][0] = dinc.inc(F_V, ci, cj, var);      g[1][0] = dinc.inc(F_EH, ci, cj, var);
-            g[2][0] = dinc.inc(F_V, ci + 1, cj, var);  g[0][1] = dinc.inc(F_EV, ci, cj, var);
-            g[1][1] = dinc.inc(F_C, ci, cj, var);      g[2][1] = dinc.inc(F_EV, ci + 1, cj, var);
-            g[0][2] = dinc.inc(F_V, ci, cj + 1, var);  g[1][2] = dinc.inc(F_EH, ci, cj + 1, var);
-            g[2][2] = dinc.inc(F_V, ci + 1, cj + 1, var);
-            T val = q2(xm, xp, ym, yp, g);
-            if (var == 0) du = val; else if (var == 1) dv = val; else dp = val;
-        }
+        cell_inc(dinc, ci, cj, 0, g);
+        du = q2(xm, xp, ym, yp, g);
+        cell_inc(dinc, ci, cj, 1, g);
+        dv = q2(xm, xp, ym, yp, g);
+        cell_inc(dinc, ci, cj, 2, g);
+        dp = q2(xm, xp, ym, yp, g);
         rho_over_c2 = quot(pol.rho(Wf.r), pol.gamma * pol.pr(Wf.p));    // 1 / c^2 at the foot
     } else {
         du = dinc.inc(fam, i, j, 0);
@@ -288,7 +336,8 @@ AF_HD Prim<T> point_update_f(const A& acc, const D& dinc, int fam, int i, int j,
         dp = dinc.inc(fam, i, j, 2);
         rho_over_c2 = quot(pol.rho(WP.r), pol.gamma * pol.pr(WP.p));    // frozen 1 / c^2 at P
     }
-    return Prim<T>{Wf.r + dp * rho_over_c2, Wf.u + du, Wf.v + dv, Wf.p + dp};
+    if constexpr (SUM) return Prim<T>{Wf.r + dp * rho_over_c2, du, dv, Wf.p + dp};
+    else return Prim<T>{Wf.r + dp * rho_over_c2, Wf.u + du, Wf.v + dv, Wf.p + dp};
 }
 
 template <int FAM, int SCHEME, class T, class A, class D, class Pol>
@@ -301,7 +350,7 @@ AF_HD Prim<T> point_update(const A& acc, const D& dinc, int i, int j, const Pol&
 // nine nodes and both increment sets are gathered once and every stage is checked
 // to stay in it.  Lanes whose feet leave it take the general path above, which
 // performs the same arithmetic (so the results do not depend on the path).
-template <int SCHEME, class T, class A, class D, class Pol>
+template <int SCHEME, bool SUM = false, class T, class A, class D, class Pol>
 AF_HD void point_update_pair_f(const A& acc, const D& d0, const D& d1, int fam, int i, int j, const Pol& pol,
                                T lam0, T lam1, unsigned& st, Prim<T>& wh, Prim<T>& w1) {
     const T ox = fam_ox<T>(fam), oy = fam_oy<T>(fam);
@@ -317,77 +366,78 @@ AF_HD void point_update_pair_f(const A& acc, const D& d0, const D& d1, int fam, 
         cx = (int)fcx;
         cy = (int)fcy;
         const int ci = i + cx, cj = j + cy;
-        T fr[3][3], fu[3][3], fv[3][3], fp[3][3];
+        // field by field, so that nine nodal values are live at a time: the velocities (both
+        // Picard stages' positions), then density, pressure and the increments at the feet
+        T xm[2], xp[2], ym[2], yp[2], g[3][3];
+        Prim<T> Wf[2];
         {
-            Prim<T> n[3][3];
-            cell_nodes<T>(acc, ci, cj, n);
+            T fu[3][3], fv[3][3];
+            cell_field<1>(acc, ci, cj, fu);
+            cell_field<2>(acc, ci, cj, fv);
 #pragma unroll
-            for (int a = 0; a < 3; ++a)
-#pragma unroll
-                for (int b = 0; b < 3; ++b) {
-                    fr[a][b] = n[a][b].r; fu[a][b] = n[a][b].u; fv[a][b] = n[a][b].v; fp[a][b] = n[a][b].p;
+            for (int t = 0; t < 2; ++t) {
+                const T lam = t ? lam1 : lam0;
+                T xi, eta, fl;
+                // first Picard stage
+                const T o1x = ox - lam * uP, o1y = oy - lam * vP;
+                fl = floor(o1x); fast = fast && (fl == fcx); xi = T(2) * (o1x - fl) - T(1);
+                fl = floor(o1y); fast = fast && (fl == fcy); eta = T(2) * (o1y - fl) - T(1);
+                lag_pm(xi, xm[t], xp[t]);
+                lag_pm(eta, ym[t], yp[t]);
+                const T u1 = q2(xm[t], xp[t], ym[t], yp[t], fu), v1 = q2(xm[t], xp[t], ym[t], yp[t], fv);
+                // second stage
+                const T o2x = ox - lam * pol.vu(u1), o2y = oy - lam * pol.vv(v1);
+                fast = fast && (fabs(o2x - ox) < T(1)) && (fabs(o2y - oy) < T(1));
+                fl = floor(o2x); fast = fast && (fl == fcx); xi = T(2) * (o2x - fl) - T(1);
+                fl = floor(o2y); fast = fast && (fl == fcy); eta = T(2) * (o2y - fl) - T(1);
+                lag_pm(xi, xm[t], xp[t]);
+                lag_pm(eta, ym[t], yp[t]);
+                if constexpr (!SUM) {
+                    Wf[t].u = q2(xm[t], xp[t], ym[t], yp[t], fu);
+                    Wf[t].v = q2(xm[t], xp[t], ym[t], yp[t], fv);
                 }
+            }
         }
+        cell_field<3>(acc, ci, cj, g);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) Wf[t].r = q2(xm[t], xp[t], ym[t], yp[t], g);
+        cell_field<0>(acc, ci, cj, g);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) Wf[t].p = q2(xm[t], xp[t], ym[t], yp[t], g);
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-            const T lam = t ? lam1 : lam0;
-            T xi, eta, xm, xp, ym, yp, fl;
-            // first Picard stage
-            T o1x = ox - lam * uP, o1y = oy - lam * vP;
-            fl = floor(o1x); fast = fast && (fl == fcx); xi = T(2) * (o1x - fl) - T(1);
-            fl = floor(o1y); fast = fast && (fl == fcy); eta = T(2) * (o1y - fl) - T(1);
-            lag_pm(xi, xm, xp);
-            lag_pm(eta, ym, yp);
-            const T u1 = q2(xm, xp, ym, yp, fu), v1 = q2(xm, xp, ym, yp, fv);
-            // second stage
-            T o2x = ox - lam * pol.vu(u1), o2y = oy - lam * pol.vv(v1);
-            fast = fast && (fabs(o2x - ox) < T(1)) && (fabs(o2y - oy) < T(1));
-            fl = floor(o2x); fast = fast && (fl == fcx); xi = T(2) * (o2x - fl) - T(1);
-            fl = floor(o2y); fast = fast && (fl == fcy); eta = T(2) * (o2y - fl) - T(1);
-            lag_pm(xi, xm, xp);
-            lag_pm(eta, ym, yp);
-            Prim<T> Wf{q2(xm, xp, ym, yp, fr), q2(xm, xp, ym, yp, fu), q2(xm, xp, ym, yp, fv), q2(xm, xp, ym, yp, fp)};
-            T du, dv, dp, rho_over_c2;
+            const D& dd = t ? d1 : d0;
+            T d[3];
             if constexpr (SCHEME == 0) {
-                // increments of the candidate cell's nine nodes for this duration,
-                // gathered per duration to bound the live set
-                const D& dd = t ? d1 : d0;
-                T g[3][3][3];
 #pragma unroll
                 for (int var = 0; var < 3; ++var) {
-                    g[var][0][0] = dd.inc(F_V, ci, cj, var);      g[var][1][0] = dd.inc(F_EH, ci, cj, var);
-                    g[var][2][0] = dd.inc(F_V, ci + 1, cj, var);  g[var][0][1] = dd.inc(F_EV, ci, cj, var);
-                    g[var][1][1] = dd.inc(F_C, ci, cj, var);      g[var][2][1] = dd.inc(F_EV, ci + 1, cj, var);
-                    g[var][0][2] = dd.inc(F_V, ci, cj + 1, var);  g[var][1][2] = dd.inc(F_EH, ci, cj + 1, var);
-                    g[var][2][2] = dd.inc(F_V, ci + 1, cj + 1, var);
+                    cell_inc(dd, ci, cj, var, g);
+                    d[var] = q2(xm[t], xp[t], ym[t], yp[t], g);
                 }
-                du = q2(xm, xp, ym, yp, g[0]);
-                dv = q2(xm, xp, ym, yp, g[1]);
-                dp = q2(xm, xp, ym, yp, g[2]);
-                rho_over_c2 = quot(pol.rho(Wf.r), pol.gamma * pol.pr(Wf.p));
             } else {
-                const D& dd = t ? d1 : d0;
-                du = dd.inc(fam, i, j, 0);
-                dv = dd.inc(fam, i, j, 1);
-                dp = dd.inc(fam, i, j, 2);
-                rho_over_c2 = quot(pol.rho(WP.r), pol.gamma * pol.pr(WP.p));
+#pragma unroll
+                for (int var = 0; var < 3; ++var) d[var] = dd.inc(fam, i, j, var);
             }
-            wr[t] = Prim<T>{Wf.r + dp * rho_over_c2, Wf.u + du, Wf.v + dv, Wf.p + dp};
+            // 1 / c^2 at the foot (transported) or frozen at the target (additive)
+            const T rho_over_c2 = SCHEME == 0 ? quot(pol.rho(Wf[t].r), pol.gamma * pol.pr(Wf[t].p))
+                                              : quot(pol.rho(WP.r), pol.gamma * pol.pr(WP.p));
+            if constexpr (SUM) wr[t] = Prim<T>{Wf[t].r + d[2] * rho_over_c2, d[0], d[1], Wf[t].p + d[2]};
+            else wr[t] = Prim<T>{Wf[t].r + d[2] * rho_over_c2, Wf[t].u + d[0], Wf[t].v + d[1], Wf[t].p + d[2]};
         }
     }
     if (fast) {
         wh = wr[0];
         w1 = wr[1];
     } else {
-        wh = point_update_f<SCHEME>(acc, d0, fam, i, j, pol, lam0, st);
-        w1 = point_update_f<SCHEME>(acc, d1, fam, i, j, pol, lam1, st);
+        wh = point_update_f<SCHEME, SUM>(acc, d0, fam, i, j, pol, lam0, st);
+        w1 = point_update_f<SCHEME, SUM>(acc, d1, fam, i, j, pol, lam1, st);
     }
 }
 
-template <int FAM, int SCHEME, class T, class A, class D, class Pol>
+template <int FAM, int SCHEME, bool SUM = false, class T, class A, class D, class Pol>
 AF_HD void point_update_pair(const A& acc, const D& d0, const D& d1, int i, int j, const Pol& pol, T lam0, T lam1,
                              unsigned& st, Prim<T>& wh, Prim<T>& w1) {
-    point_update_pair_f<SCHEME>(acc, d0, d1, FAM, i, j, pol, lam0, lam1, st, wh, w1);
+    point_update_pair_f<SCHEME, SUM>(acc, d0, d1, FAM, i, j, pol, lam0, lam1, st, wh, w1);
 }
 
 }  // namespace af

@@ -131,12 +131,13 @@ int main() {
     const long incE = total() - c0 - incV - incC;
     c0 = total();
     Prim<Cnt> w[3][2];
-    w[0][0] = point_update<F_V, 0>(A, D, 2, 2, pol, lam0, st);
-    w[0][1] = point_update<F_V, 0>(A, D, 2, 2, pol, lam1, st);
-    w[1][0] = point_update<F_EV, 0>(A, D, 2, 2, pol, lam0, st);
-    w[1][1] = point_update<F_EV, 0>(A, D, 2, 2, pol, lam1, st);
-    w[2][0] = point_update<F_EH, 0>(A, D, 2, 2, pol, lam0, st);
-    w[2][1] = point_update<F_EH, 0>(A, D, 2, 2, pol, lam1, st);
+    // the velocities' increments enter as u + du and v + dv (formed once per node)
+    const int fam[3] = {F_V, F_EV, F_EH};
+    for (int f = 0; f < 3; ++f) {
+        w[f][0] = point_update_f<0, true>(A, D, fam[f], 2, 2, pol, lam0, st);
+        w[f][1] = point_update_f<0, true>(A, D, fam[f], 2, 2, pol, lam1, st);
+    }
+    for (int k = 0; k < 4 * 2 * 2; ++k) (void)(w[0][0].u + w[0][1].u);
     long points = total() - c0;
     c0 = total();
     // time-Simpson fluxes of the owned targets: V (F and G), Ev (F), Eh (G)
