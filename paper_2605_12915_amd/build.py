@@ -24,8 +24,12 @@ FLAGS = [
     "-munsafe-fp-atomics", f"-I{CSRC}", f"-I{INCLUDE}",
 ]
 # FP contraction: free (across statements) for the FP64 kernels; within source
-# expressions only for the two FP32 step kernels, which must round identically.
-CONTRACT_ON = {"af_fused_f32.hip", "af_batch.hip"}
+# expressions only for the FP32 step kernels, which must round identically.
+CONTRACT_ON = {"af_fused_f32.hip", "af_fused_f32_small.hip", "af_batch.hip"}
+# Files whose LDS reads stay single: a ds_read2_b64 holds the LDS for 8.2 cycles, two
+# ds_read_b64 for 4.7 (16 waves per CU).  The FP32 31x10 and batch kernels are the faster with
+# paired reads, which cost them no LDS cycles and save issue slots.
+SINGLE_READS = {"af_fused.hip", "af_fused_f32_small.hip"}
 
 
 # Backend options for the device code only (a plain -mllvm would also reach the host
@@ -33,13 +37,15 @@ CONTRACT_ON = {"af_fused_f32.hip", "af_batch.hip"}
 # faster on the step, FP32 and adjoint kernels than the default.  The device pass writes
 # the offload bundle that the host pass embeds.
 DEVICE_ONLY = ["-mllvm", "-misched=gcn-max-ilp"]
+UNPAIRED = ["-Xclang", "-target-feature", "-Xclang", "-load-store-opt", "-mllvm", "-amdgpu-load-store-vectorizer=0"]
 
 
 def _compile(src: str, verbose: bool) -> str:
     obj = os.path.join(OBJ, os.path.basename(src) + ".o")
     dev = os.path.join(OBJ, os.path.basename(src) + ".hipfb")
     contract = "-ffp-contract=on" if os.path.basename(src) in CONTRACT_ON else "-ffp-contract=fast"
-    cmds = [[HIPCC, *FLAGS, contract, "--cuda-device-only", *DEVICE_ONLY, "-c", src, "-o", dev],
+    reads = UNPAIRED if os.path.basename(src) in SINGLE_READS else []
+    cmds = [[HIPCC, *FLAGS, contract, "--cuda-device-only", *DEVICE_ONLY, *reads, "-c", src, "-o", dev],
             [HIPCC, *FLAGS, contract, "--cuda-host-only", "-Xclang", "-fcuda-include-gpubinary", "-Xclang", dev,
              "-c", src, "-o", obj]]
     for cmd in cmds:

@@ -452,10 +452,10 @@ af_status af_init(const af_config* cfg, void* hip_stream, af_ctx** out) {
     if (c->variant == 1) sbytes = af::scratch_bytes_multi_f64(cfg->nx, cfg->ny);
     if (c->variant == 3) sbytes = af::scratch_bytes_fc_f64(cfg->nx, cfg->ny);
     if (c->variant == 2) sbytes = af::scratch_bytes_split_f64(cfg->nx, cfg->ny);
-    if (e == hipSuccess && c->f32) e = af::prepare_fused_f32();
+    if (e == hipSuccess && c->f32) e = af::prepare_fused_f32(cfg->nx, cfg->ny);
     if (e == hipSuccess && c->f32) e = hipMalloc(&c->comp, 4 * c->N * sizeof(float));
     if (e == hipSuccess && c->f32) e = af::launch_zero(c->comp, 4 * c->N * sizeof(float), c->stream);
-    if (e == hipSuccess && !c->f32 && c->variant == 0) e = af::prepare_fused_f64();
+    if (e == hipSuccess && !c->f32 && c->variant == 0) e = af::prepare_fused_f64(cfg->nx, cfg->ny);
     if (e == hipSuccess && !c->f32) e = af::prepare_adjoint_f64();
     if (e == hipSuccess && c->variant == 2) e = af::prepare_split_f64();
     if (e == hipSuccess) e = hipMalloc(&c->state2, 16 * c->N * c->elem);
@@ -935,14 +935,21 @@ const char* af_dominant_kernel(af_ctx* c) {
         return c->kname.c_str();
     }
     const bool rb = c && (c->cfg.flags & AF_SCHEME_RB);
+    const bool small = c && af::small_grid(c->f32, c->cfg.nx, c->cfg.ny);
+    if (c && c->f32 && small)
+        return rb ? "af::k_fused<float, af::PolPert<float>, 8, 8, 256, 1, true, 4, 0, true, true>"
+                  : "af::k_fused<float, af::PolPert<float>, 8, 8, 256, 0, true, 4, 0, true, true>";
     if (c && c->f32)
-        return rb ? "af::k_fused<float, af::PolPert<float>, 31, 10, 512, 1, true, 4, 32, true>"
-                  : "af::k_fused<float, af::PolPert<float>, 31, 10, 512, 0, true, 4, 32, true>";
+        return rb ? "af::k_fused<float, af::PolPert<float>, 31, 10, 512, 1, true, 4, 32, true, false>"
+                  : "af::k_fused<float, af::PolPert<float>, 31, 10, 512, 0, true, 4, 32, true, false>";
     if (c && c->variant == 3) return "af::k_fc_points";
     if (c && c->variant == 1) return "af_step multi-kernel sequence";
     if (c && c->variant == 2) return rb ? "af::k_points_update<32, 8, 512, 1>" : "af::k_points_update<32, 8, 512, 0>";
-    return rb ? "af::k_fused<double, af::PolAbs<double>, 31, 10, 512, 1, false, 1, 32, true>"
-              : "af::k_fused<double, af::PolAbs<double>, 31, 10, 512, 0, false, 1, 32, true>";
+    if (small)
+        return rb ? "af::k_fused<double, af::PolAbs<double>, 8, 8, 256, 1, false, 1, 0, true, true>"
+                  : "af::k_fused<double, af::PolAbs<double>, 8, 8, 256, 0, false, 1, 0, true, true>";
+    return rb ? "af::k_fused<double, af::PolAbs<double>, 15, 10, 512, 1, false, 4, 16, true, true>"
+              : "af::k_fused<double, af::PolAbs<double>, 15, 10, 512, 0, false, 4, 16, true, true>";
 }
 
 }  // extern "C"

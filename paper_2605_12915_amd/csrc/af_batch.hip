@@ -25,9 +25,8 @@ __device__ __noinline__ unsigned batch_tile(const BatchInst* __restrict__ inst, 
     const BatchInst& d = inst[it.x];
     const PlaneView in{{d.S[parity]}}, out{{d.S[parity ^ 1]}};
     unsigned st = 0;
-    fused_tile<float, PolPert<float>, TX, TY, NT, SCHEME, true>(L, in, out, d.comp, d.nx, d.ny,
-                                                                (it.y % d.tiles_x) * TX, (it.y / d.tiles_x) * TY,
-                                                                d.pol, d.lam0, d.lam1, st);
+    fused_tile<NT, SCHEME, true>(L, in, out, d.comp, d.nx, d.ny, (it.y % d.tiles_x) * TX, (it.y / d.tiles_x) * TY, d.pol,
+                                 d.lam0, d.lam1, st);
     return st;
 }
 
@@ -75,8 +74,8 @@ __global__ void __launch_bounds__(NT, MINW) k_fused_batch_direct(const BatchInst
     const BatchInst& d = inst[it.x];
     const PlaneView in{{d.S[parity]}}, out{{d.S[parity ^ 1]}};
     unsigned st = 0;
-    fused_tile<float, PolPert<float>, TX, TY, NT, SCHEME, true, RW, (RW > 0)>(
-        L, in, out, d.comp, d.nx, d.ny, (it.y % d.tiles_x) * TX, (it.y / d.tiles_x) * TY, d.pol, d.lam0, d.lam1, st);
+    fused_tile<NT, SCHEME, true, RW, (RW > 0)>(L, in, out, d.comp, d.nx, d.ny, (it.y % d.tiles_x) * TX,
+                                               (it.y / d.tiles_x) * TY, d.pol, d.lam0, d.lam1, st);
     if (st) atomicOr(status, st);
 }
 

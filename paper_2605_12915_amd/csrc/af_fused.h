@@ -4,6 +4,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "af_internal.h"
 #include "af_kernels.h"
 #include "af_tile.h"
@@ -32,12 +34,11 @@ __device__ __forceinline__ void store_prim(const SP& o, size_t g, const Prim<T>&
 // feet at a common offset).  DYN: the family of a target is a run-time value, so a
 // wavefront holding targets of two families runs one instruction stream instead of
 // both families' code one after the other.
-template <class T, class Pol, int TX, int TY, int NT, int SCHEME, bool KAHAN, int RW = 0, bool DYN = false,
-          class SP>
-__device__ __forceinline__ void fused_tile(FusedTile<T, TX, TY>& L, const SP& in, const SP& out,
-                                           T* comp, int nx, int ny, int i0, int j0, const Pol pol, T lam0, T lam1,
-                                           unsigned& st) {
-    using Tile = FusedTile<T, TX, TY>;
+template <int NT, int SCHEME, bool KAHAN, int RW = 0, bool DYN = false, class Tile, class Pol, class SP,
+          class T = typename Tile::S>
+__device__ __forceinline__ void fused_tile(Tile& L, const SP& in, const SP& out, T* comp, int nx, int ny, int i0,
+                                           int j0, const Pol pol, T lam0, T lam1, unsigned& st) {
+    constexpr int TX = Tile::X, TY = Tile::Y;
     const int tid = threadIdx.x;
 
     // windows reach 2 cells below and 3 above the tile: one wrap suffices when the
@@ -49,7 +50,7 @@ __device__ __forceinline__ void fused_tile(FusedTile<T, TX, TY>& L, const SP& in
         // every round's loads issued before the first store: the window has slightly more
         // node-cells than threads, and a second load round trip would hold the whole
         // workgroup at the barrier (1.5% faster; in FP32 the extra live registers cost more)
-        constexpr int NP0 = Tile::PX * Tile::PY, R0 = (NP0 + NT - 1) / NT;
+        constexpr int R0 = (Tile::NSTAGE + NT - 1) / NT;
         T pv[R0][12];
 #pragma unroll
         for (int r = 0; r < R0; ++r) {
@@ -67,23 +68,23 @@ __device__ __forceinline__ void fused_tile(FusedTile<T, TX, TY>& L, const SP& in
             int x, y;
             if (Tile::stage_item(e, x, y))
 #pragma unroll
-                for (int k = 0; k < 12; ++k) L.P[k][y][x] = pv[r][k];
+                for (int k = 0; k < 12; ++k) L.p(k, y, x) = pv[r][k];
         }
     } else {
-        for (int e = tid; e < Tile::PX * Tile::PY; e += NT) {
+        for (int e = tid; e < Tile::NSTAGE; e += NT) {
             int x, y;
             Tile::stage_item(e, x, y);
             const size_t g = (size_t)wrap_win(j0 + y - 2, ny, oney) * nx + wrap_win(i0 + x - 2, nx, onex);
 #pragma unroll
-            for (int k = 0; k < 12; ++k) L.P[k][y][x] = in.p[4 + k][g];
+            for (int k = 0; k < 12; ++k) L.p(k, y, x) = in.p[4 + k][g];
         }
     }
     __syncthreads();
 
     // ---- phase 1: recovered centres of cells [-2, T+2)^2 ------------------------------
     {
-        LdsAcc<T, TX, TY> A{&L};
-        for (int e = tid; e < Tile::SC * Tile::CY; e += NT) {
+        TileAcc<Tile> A{&L};
+        for (int e = tid; e < Tile::NCENTRE; e += NT) {
             int x, y;
             if (!Tile::centre_item(e, x, y)) continue;
             const size_t g = (size_t)wrap_win(j0 + y, ny, oney) * nx + wrap_win(i0 + x, nx, onex);
@@ -92,10 +93,10 @@ __device__ __forceinline__ void fused_tile(FusedTile<T, TX, TY>& L, const SP& in
                                    A.node(F_V, x + 1, y + 1), A.node(F_EH, x, y), A.node(F_EH, x, y + 1),
                                    A.node(F_EV, x, y), A.node(F_EV, x + 1, y));
             if (!(pol.rho(w.r) > T(0)) || !(pol.pr(w.p) > T(0))) st |= SB_NONPHYS;
-            L.C[0][y + 2][x + 2] = w.r;
-            L.C[1][y + 2][x + 2] = w.u;
-            L.C[2][y + 2][x + 2] = w.v;
-            L.C[3][y + 2][x + 2] = w.p;
+            L.c(0, y + 2, x + 2) = w.r;
+            L.c(1, y + 2, x + 2) = w.u;
+            L.c(2, y + 2, x + 2) = w.v;
+            L.c(3, y + 2, x + 2) = w.p;
         }
     }
     __syncthreads();
@@ -104,14 +105,14 @@ __device__ __forceinline__ void fused_tile(FusedTile<T, TX, TY>& L, const SP& in
     // (transported update: the velocities' planes hold u + du and v + dv)
     constexpr bool kSum = SCHEME == 0;
     {
-        LdsAcc<T, TX, TY> A{&L};
-        constexpr int NI = (Tile::SD * Tile::DY + 63) / 64 * 64;   // items of one pair, in whole wavefronts
+        TileAcc<Tile> A{&L};
+        constexpr int NI = (Tile::NINCR + 63) / 64 * 64;   // items of one pair, in whole wavefronts
         int x, y;
         auto put = [&](int pl, T v) {
             const int fam = (pl % 12) / 3, q = pl % 3;
             if (kSum && q == 0) v = A.node(fam, x, y).u + v;
             if (kSum && q == 1) v = A.node(fam, x, y).v + v;
-            L.D[pl / 12][pl % 12][y + 1][x + 1] = v;
+            if (Tile::has_d(pl % 12, y + 1)) L.d(pl / 12, pl % 12, y + 1, x + 1) = v;
         };
         if constexpr (NT >= 2 * NI) {
             // threads enough for both pairs of families at once, one pair per wavefront
@@ -121,7 +122,7 @@ __device__ __forceinline__ void fused_tile(FusedTile<T, TX, TY>& L, const SP& in
                 if (Tile::incr_item(tid - NI, x, y)) put_pair<3>(A, x, y, pol, lam0, lam1, st, put);
             }
         } else {
-            for (int e = tid; e < Tile::SD * Tile::DY; e += NT)
+            for (int e = tid; e < Tile::NINCR; e += NT)
                 if (Tile::incr_item(e, x, y)) cell_increments(A, x, y, pol, lam0, lam1, st, put);
         }
     }
@@ -134,8 +135,8 @@ __device__ __forceinline__ void fused_tile(FusedTile<T, TX, TY>& L, const SP& in
     constexpr int ROUNDS = (NITEMS + NT - 1) / NT;
     T fres[ROUNDS][8];
     {
-        LdsAcc<T, TX, TY> A{&L};
-        LdsInc<T, TX, TY> D0{&L, 0}, D1{&L, 1};
+        TileAcc<Tile> A{&L};
+        TileInc<Tile> D0{&L, 0}, D1{&L, 1};
 #pragma unroll
         for (int r = 0; r < ROUNDS; ++r) {
             const int e = r * NT + tid;
@@ -284,15 +285,18 @@ __device__ __forceinline__ void fused_tile(FusedTile<T, TX, TY>& L, const SP& in
     }
 }
 
+template <class T, int TX, int TY, bool PACK>
+using StepTile = std::conditional_t<PACK, PackedTile<T, TX, TY>, FusedTile<T, TX, TY>>;
+
 // ---- single-grid kernel: one tile per workgroup --------------------------------------
 // MINW: minimum wavefronts per SIMD the register allocation must allow (1: no
 // constraint beyond the workgroup size; 4 at 512 threads: two workgroups per CU).
 template <class T, class Pol, int TX, int TY, int NT, int SCHEME, bool KAHAN, int MINW = 1, int RW = 0,
-          bool DYN = false>
+          bool DYN = false, bool PACK = false>
 __global__ void __launch_bounds__(NT, MINW) k_fused(StatePtrs<T> in, StatePtrs<T> out, T* comp, int nx, int ny,
                                               int tiles_x, int ntiles, Pol pol, T lam0, T lam1, unsigned* status) {
     extern __shared__ __align__(16) unsigned char smem[];
-    auto& L = *reinterpret_cast<FusedTile<T, TX, TY>*>(smem);
+    auto& L = *reinterpret_cast<StepTile<T, TX, TY, PACK>*>(smem);
     // XCD-aware numbering: hardware dispatches consecutive workgroups round-robin over
     // the 8 XCDs; give each XCD a contiguous run of tiles.
     int tile;
@@ -303,39 +307,41 @@ __global__ void __launch_bounds__(NT, MINW) k_fused(StatePtrs<T> in, StatePtrs<T
         tile = base + (b >> 3);
     }
     unsigned st = 0;
-    fused_tile<T, Pol, TX, TY, NT, SCHEME, KAHAN, RW, DYN>(L, in, out, comp, nx, ny, (tile % tiles_x) * TX,
-                                                           (tile / tiles_x) * TY, pol, lam0, lam1, st);
+    fused_tile<NT, SCHEME, KAHAN, RW, DYN>(L, in, out, comp, nx, ny, (tile % tiles_x) * TX, (tile / tiles_x) * TY, pol,
+                                           lam0, lam1, st);
     if (st) atomicOr(status, st);
 }
 
 
-template <class T, class Pol, int TX, int TY, int NT, bool KAHAN, int MINW = 1, int RW = 0, bool DYN = false>
+template <class T, class Pol, int TX, int TY, int NT, bool KAHAN, int MINW = 1, int RW = 0, bool DYN = false,
+          bool PACK = false>
 hipError_t launch_fused(const StepArgs& a, const Pol& pol) {
     StatePtrs<T> in, out;
     for (int k = 0; k < 16; ++k) { in.p[k] = (T*)a.in[k]; out.p[k] = (T*)a.out[k]; }
     const int tiles_x = (a.nx + TX - 1) / TX, tiles_y = (a.ny + TY - 1) / TY;
     const int ntiles = tiles_x * tiles_y;
     const T lam1 = T(a.dt / a.h), lam0 = T(0.5 * a.dt / a.h);
-    const size_t lds = sizeof(FusedTile<T, TX, TY>);
+    const size_t lds = sizeof(StepTile<T, TX, TY, PACK>);
     T* comp = (T*)a.comp;
     if (a.ev_begin) (void)hipEventRecord(a.ev_begin, a.stream);
     if (a.scheme == 0)
-        hipLaunchKernelGGL((k_fused<T, Pol, TX, TY, NT, 0, KAHAN, MINW, RW, DYN>), dim3(ntiles), dim3(NT), lds, a.stream, in, out, comp,
+        hipLaunchKernelGGL((k_fused<T, Pol, TX, TY, NT, 0, KAHAN, MINW, RW, DYN, PACK>), dim3(ntiles), dim3(NT), lds, a.stream, in, out, comp,
                            a.nx, a.ny, tiles_x, ntiles, pol, lam0, lam1, a.status);
     else
-        hipLaunchKernelGGL((k_fused<T, Pol, TX, TY, NT, 1, KAHAN, MINW, RW, DYN>), dim3(ntiles), dim3(NT), lds, a.stream, in, out, comp,
+        hipLaunchKernelGGL((k_fused<T, Pol, TX, TY, NT, 1, KAHAN, MINW, RW, DYN, PACK>), dim3(ntiles), dim3(NT), lds, a.stream, in, out, comp,
                            a.nx, a.ny, tiles_x, ntiles, pol, lam0, lam1, a.status);
     if (a.ev_end) (void)hipEventRecord(a.ev_end, a.stream);
     return hipGetLastError();
 }
 
-template <class T, class Pol, int TX, int TY, int NT, bool KAHAN, int MINW = 1, int RW = 0, bool DYN = false>
+template <class T, class Pol, int TX, int TY, int NT, bool KAHAN, int MINW = 1, int RW = 0, bool DYN = false,
+          bool PACK = false>
 hipError_t prepare_fused() {
-    const size_t lds = sizeof(FusedTile<T, TX, TY>);
-    hipError_t e = hipFuncSetAttribute((const void*)k_fused<T, Pol, TX, TY, NT, 0, KAHAN, MINW, RW, DYN>,
+    const size_t lds = sizeof(StepTile<T, TX, TY, PACK>);
+    hipError_t e = hipFuncSetAttribute((const void*)k_fused<T, Pol, TX, TY, NT, 0, KAHAN, MINW, RW, DYN, PACK>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    return hipFuncSetAttribute((const void*)k_fused<T, Pol, TX, TY, NT, 1, KAHAN, MINW, RW, DYN>,
+    return hipFuncSetAttribute((const void*)k_fused<T, Pol, TX, TY, NT, 1, KAHAN, MINW, RW, DYN, PACK>,
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
 

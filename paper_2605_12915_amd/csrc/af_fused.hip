@@ -24,24 +24,36 @@
 
 namespace af {
 
-// 31x10 cells, 512 threads (154 KB of LDS, one workgroup per CU).  Row stride of the
-// staged arrays 36 words; phase 2 has 34x13 = 442 node-cells (one round) and phase 3
-// places every target family in rows of 32 lanes: 32x11 V, 32x10 Ev and 31(+1)x11 Eh
-// targets fill exactly two rounds of 512, and a half-wavefront (the lanes the LDS
-// serves together) reads one row of 32 consecutive doubles (all 64 banks).  The family is a run-time value
-// in phase 3 (DYN), so the two wavefronts that hold targets of two families run one
-// instruction stream.  Measured at 2048^2 against the earlier 26x12 tile with tight
-// item rows and the family as a template constant (1.030 ms): the run-time family
-// alone 0.968 ms, the 31x10 rows alone 1.011 ms, both 0.963 ms.
-constexpr int kTX = 31, kTY = 10, kNT = 512, kRW = 32;
+// 15x10 cells, 512 threads, the packed tile (79 KB of LDS) and at most 128 registers: two
+// workgroups share a CU, four waves per SIMD.  With one workgroup per CU (31x10 cells, 512
+// threads, 256 registers, two waves per SIMD) the step was bound by latency: the vector
+// units were busy 51% of the cycles, the rest went to barriers, LDS and global round
+// trips of one workgroup that nothing overlapped.  Two independent workgroups overlap
+// each other's phases and four waves hide the LDS latency (vector units 72% busy),
+// which outweighs the larger halo (18x13 node-cells for 150 cells, 1.56 per cell, against
+// 1.43).  Phase 2 gives each wavefront one pair of node families (234 node-cells x 2
+// pairs in 2 x 256 lanes), phase 3 one target to a lane: 16x11 V, 16x10 Ev and 15(+1)x11
+// Eh targets are exactly 512.  This file is compiled without merging LDS reads in pairs:
+// a ds_read2_b64 takes 8.2 cycles of the LDS, two ds_read_b64 4.7 (measured at 16 waves per
+// CU).  2048^2 step on one GPU: 31x10 0.79 ms; 31x10 with 1024 threads 0.76, unpaired reads 0.73;
+// 15x9 unpacked at two workgroups per CU 0.72, unpaired reads 0.68; 15x10 packed 0.73, unpaired 0.62.
+constexpr int kTX = 15, kTY = 10, kNT = 512, kRW = 16, kMinW = 4;
+// Grids whose 8x8 tiles do not outnumber the CUs: one such tile per CU, whose phases are
+// single rounds of one wave per SIMD, is the shorter chain (us per step with 15x10
+// and 8x8 tiles: 64^2 9.8 and 7.9, 96^2 10.0 and 8.2, 128^2 (256 tiles) 10.4 and 8.6; beyond, at
+// 192^2, 14.9 and 16.0).
+constexpr int kSX = 8, kSY = 8, kSNT = 256;
 
 hipError_t launch_step_fused_f64(const StepArgs& a) {
     PolAbs<double> pol{a.gamma, 1.0 / (a.gamma - 1.0)};
-    return launch_fused<double, PolAbs<double>, kTX, kTY, kNT, false, 1, kRW, true>(a, pol);
+    if (small_grid(false, a.nx, a.ny))
+        return launch_fused<double, PolAbs<double>, kSX, kSY, kSNT, false, 1, 0, true, true>(a, pol);
+    return launch_fused<double, PolAbs<double>, kTX, kTY, kNT, false, kMinW, kRW, true, true>(a, pol);
 }
 
-hipError_t prepare_fused_f64() { return prepare_fused<double, PolAbs<double>, kTX, kTY, kNT, false, 1, kRW, true>(); }
-
-size_t fused_lds_bytes() { return sizeof(FusedTile<double, kTX, kTY>); }
+hipError_t prepare_fused_f64(int nx, int ny) {
+    if (small_grid(false, nx, ny)) return prepare_fused<double, PolAbs<double>, kSX, kSY, kSNT, false, 1, 0, true, true>();
+    return prepare_fused<double, PolAbs<double>, kTX, kTY, kNT, false, kMinW, kRW, true, true>();
+}
 
 }  // namespace af

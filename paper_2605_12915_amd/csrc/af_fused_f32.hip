@@ -33,10 +33,12 @@ PolPert<float> pert_pol_f32(const double bg[4], double g) {
 }
 
 hipError_t launch_step_fused_f32(const StepArgs& a) {
+    if (small_grid(true, a.nx, a.ny)) return launch_step_fused_f32_small(a);
     return launch_fused<float, PolPert<float>, kFTX, kFTY, kFNT, true, kFMinW, kFRW, true>(a, pert_pol_f32(a.bg, a.gamma));
 }
 
-hipError_t prepare_fused_f32() {
+hipError_t prepare_fused_f32(int nx, int ny) {
+    if (small_grid(true, nx, ny)) return prepare_fused_f32_small();
     return prepare_fused<float, PolPert<float>, kFTX, kFTY, kFNT, true, kFMinW, kFRW, true>();
 }
 

@@ -1,0 +1,24 @@
+// FP32 step of small grids: 8x8 tiles of 256 threads, the packed tile (21 KB of LDS).  A
+// grid whose 31x10 tiles leave most CUs idle is bound by the chain of one tile's phases:
+// smaller tiles shorten it (fewer wavefronts per phase) and spread over more CUs.  us per
+// step with 31x10 and 8x8 tiles: 64^2 10.8 and 7.2, 128^2 11.2 and 7.7, 192^2 (576 tiles) 11.8 and
+// 10.6; at 256^2 (1024 tiles) 12.6 and 13.8.  Compiled without merging LDS reads in pairs
+// (64^2: 8.0 merged, 7.2 not; the 31x10 kernel is the faster with merged ones, 256^2 12.6 and
+// 13.4).  The arithmetic of a node does not depend on the tile: results are bitwise those
+// of the 31x10 kernel.
+#include <hip/hip_runtime.h>
+
+#include "af_batch.h"
+#include "af_fused.h"
+
+namespace af {
+
+hipError_t launch_step_fused_f32_small(const StepArgs& a) {
+    return launch_fused<float, PolPert<float>, 8, 8, 256, true, 4, 0, true, true>(a, pert_pol_f32(a.bg, a.gamma));
+}
+
+hipError_t prepare_fused_f32_small() {
+    return prepare_fused<float, PolPert<float>, 8, 8, 256, true, 4, 0, true, true>();
+}
+
+}  // namespace af

@@ -53,10 +53,17 @@ hipError_t launch_adjoint_noalloc(StepArgs a, const void* const cot1[16], void* 
 hipError_t noalloc_scratch_ptr(void** out);
 hipError_t launch_step_fused_f64(const StepArgs& a);
 hipError_t launch_step_fused_f32(const StepArgs& a);
-hipError_t prepare_fused_f32();
-hipError_t prepare_fused_f64();
+hipError_t launch_step_fused_f32_small(const StepArgs& a);
+hipError_t prepare_fused_f32(int nx, int ny);
+hipError_t prepare_fused_f32_small();
+// Grids stepped by the 8x8-tile kernels: at most one tile per CU of the 256 in FP64, at most
+// 640 tiles in FP32 (several share a CU); both sides are measured at the kernels.
+inline bool small_grid(bool f32, int nx, int ny) {
+    const long long tiles = ((nx + 7LL) / 8) * ((ny + 7LL) / 8);
+    return tiles <= (f32 ? 640 : 256);
+}
+hipError_t prepare_fused_f64(int nx, int ny);
 hipError_t prepare_adjoint_f64();
-size_t fused_lds_bytes();
 hipError_t launch_step_split_f64(const StepArgs& a);
 hipError_t prepare_split_f64();
 size_t scratch_bytes_split_f64(int nx, int ny);

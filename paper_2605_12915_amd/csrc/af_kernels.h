@@ -94,6 +94,14 @@ AF_HD void stage_fence(T (&a1)[3][4], T (&a2)[3][4]) {
 #endif
 }
 
+// Values read before this point are read again after it instead of being kept.
+AF_HD void reload_fence() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+#endif
+}
+
 // Variable VAR (0: p, 1: u, 2: v, 3: rho) at (a, b) half cells from the vertex of cell (i, j).
 template <int VAR, class T, class A>
 AF_HD T lattice(const A& acc, int i, int j, int a, int b) {
@@ -392,11 +400,18 @@ AF_HD void point_update_pair_f(const A& acc, const D& d0, const D& d1, int fam, 
                 fl = floor(o2y); fast = fast && (fl == fcy); eta = T(2) * (o2y - fl) - T(1);
                 lag_pm(xi, xm[t], xp[t]);
                 lag_pm(eta, ym[t], yp[t]);
-                if constexpr (!SUM) {
-                    Wf[t].u = q2(xm[t], xp[t], ym[t], yp[t], fu);
-                    Wf[t].v = q2(xm[t], xp[t], ym[t], yp[t], fv);
-                }
             }
+        }
+        if constexpr (!SUM) {
+            // the velocities gathered a second time: kept from the first stage they would
+            // exceed 128 registers in FP64
+            reload_fence();
+            cell_field<1>(acc, ci, cj, g);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) Wf[t].u = q2(xm[t], xp[t], ym[t], yp[t], g);
+            cell_field<2>(acc, ci, cj, g);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) Wf[t].v = q2(xm[t], xp[t], ym[t], yp[t], g);
         }
         cell_field<3>(acc, ci, cj, g);
 #pragma unroll

@@ -15,6 +15,8 @@ namespace af {
 // its bank-conflict cycles had outnumbered its active LDS cycles).
 template <class T, int TX, int TY>
 struct FusedTile {
+    using S = T;
+    static constexpr int X = TX, Y = TY;
     static constexpr int PX = TX + 5, PY = TY + 5;   // primitives: cells [-2, T+3)
     static constexpr int CX = TX + 4, CY = TY + 4;   // centres:    cells [-2, T+2)
     static constexpr int DX = TX + 3, DY = TY + 3;   // increments: node-cells [-1, T+2)
@@ -30,6 +32,18 @@ struct FusedTile {
             T GE[4][VY][TX];                         // Eh nodes: G~
         } F;
     };
+
+    // element (y, x) of primitive plane k, centre plane k, increment plane q of duration t
+    AF_HD T& p(int k, int y, int x) { return P[k][y][x]; }
+    AF_HD T& c(int k, int y, int x) { return C[k][y][x]; }
+    AF_HD T& d(int t, int q, int y, int x) { return D[t][q][y][x]; }
+    AF_HD const T& p(int k, int y, int x) const { return P[k][y][x]; }
+    AF_HD const T& c(int k, int y, int x) const { return C[k][y][x]; }
+    AF_HD const T& d(int t, int q, int y, int x) const { return D[t][q][y][x]; }
+    // whether the tile holds row y of increment plane q
+    static AF_HD constexpr bool has_d(int, int) { return true; }
+    // items of phases 0, 1 and 2 (those past a region's width included)
+    static constexpr int NSTAGE = PX * PY, NCENTRE = SC * CY, NINCR = SD * DY;
 
     // Work items of the phases (item e of a workgroup's round-robin walk):
     // phase 0 stages node-cell (x, y) of P (cells x - 2, y - 2 of the tile),
@@ -73,24 +87,96 @@ struct FusedTile {
     }
 };
 
+// The same tile packed for two workgroups per CU (TX = 15, T double): the planes of a row
+// lie side by side ([y][plane][x]), and the planes that nothing reads in the last row (Ev of
+// the primitives, C of the increments) come last in a row, so that the staged Ev of that
+// row may fall on the centres' place (written after them) and the increments end early.
+// A row of all planes is an odd multiple of 16 doubles, so that the two rows of 16 items
+// that a half-wavefront touches fall on different banks; phases 1 and 2 walk their
+// regions in columns [0, 16) row by row, then the columns left over.
 template <class T, int TX, int TY>
-struct LdsAcc {
-    const FusedTile<T, TX, TY>* t;
-    AF_HD Prim<T> node(int fam, int x, int y) const {
-        if (fam == F_C) return {t->C[0][y + 2][x + 2], t->C[1][y + 2][x + 2], t->C[2][y + 2][x + 2], t->C[3][y + 2][x + 2]};
+struct PackedTile {
+    using S = T;
+    using Full = FusedTile<T, TX, TY>;
+    static constexpr int X = TX, Y = TY, W = TX >= 13 ? 16 : 8;
+    static constexpr int PX = Full::PX, PY = Full::PY, CX = Full::CX, CY = Full::CY, DX = Full::DX, DY = Full::DY;
+    static constexpr int VX = Full::VX, VY = Full::VY;
+    static constexpr int SC = PX, SD = DX;           // row strides of C, D
+    static constexpr int OC = (PY * 12 - 4) * PX;    // start of the centres
+    T PC[OC + CY * 4 * SC];
+    union {
+        T Db[(DY * 24 - 6) * SD];
+        struct {
+            T FV[8][VY][VX];
+            T FE[4][TY][VX];
+            T GE[4][VY][TX];
+        } F;
+    };
+    static_assert(4 * PX <= CY * 4 * SC, "the Ev row without a place falls on the centres");
+    // planes of a row: V, Eh, Ev; increments V, Eh, Ev, C (each family's durations together)
+    static AF_HD constexpr int slot(int fam) { return fam == F_EH ? 1 : (fam == F_EV ? 2 : fam); }
+    static AF_HD constexpr int ps(int k) { return 4 * slot(k / 4) + k % 4; }
+    static AF_HD constexpr int ds(int t, int q) { return 6 * slot(q / 3) + 3 * t + q % 3; }
+    AF_HD T& p(int k, int y, int x) { return PC[(y * 12 + ps(k)) * PX + x]; }
+    AF_HD T& c(int k, int y, int x) { return PC[OC + (y * 4 + k) * SC + x]; }
+    AF_HD T& d(int t, int q, int y, int x) { return Db[(y * 24 + ds(t, q)) * SD + x]; }
+    AF_HD const T& p(int k, int y, int x) const { return PC[(y * 12 + ps(k)) * PX + x]; }
+    AF_HD const T& c(int k, int y, int x) const { return PC[OC + (y * 4 + k) * SC + x]; }
+    AF_HD const T& d(int t, int q, int y, int x) const { return Db[(y * 24 + ds(t, q)) * SD + x]; }
+    static AF_HD constexpr bool has_d(int q, int y) { return q / 3 != F_C || y < DY - 1; }
+
+    // item e of a region of NX x NY: columns [0, W) in rows of W, then the rest
+    template <int NX, int NY>
+    static AF_HD bool split_item(int e, int& x, int& y) {
+        if (e < W * NY) {
+            x = e % W;
+            y = e / W;
+        } else {
+            x = W + (e - W * NY) % (NX - W);
+            y = (e - W * NY) / (NX - W);
+        }
+        return e < NX * NY;
+    }
+    static constexpr int NSTAGE = PX * PY, NCENTRE = CX * CY, NINCR = DX * DY;
+    static AF_HD bool stage_item(int e, int& x, int& y) { return Full::stage_item(e, x, y); }
+    static AF_HD bool centre_item(int e, int& x, int& y) {
+        const bool in = split_item<CX, CY>(e, x, y);
+        x -= 2;
+        y -= 2;
+        return in;
+    }
+    static AF_HD bool incr_item(int e, int& x, int& y) {
+        const bool in = split_item<DX, DY>(e, x, y);
+        x -= 1;
+        y -= 1;
+        return in;
+    }
+    template <int RW>
+    using Points = typename Full::template Points<RW>;
+    static AF_HD bool update_item(int e, int& x, int& y) { return Full::update_item(e, x, y); }
+};
+
+template <class Tile>
+struct TileAcc {
+    const Tile* t;
+    AF_HD Prim<typename Tile::S> node(int fam, int x, int y) const {
+        if (fam == F_C) return {t->c(0, y + 2, x + 2), t->c(1, y + 2, x + 2), t->c(2, y + 2, x + 2), t->c(3, y + 2, x + 2)};
         const int b = 4 * fam;
-        return {t->P[b][y + 2][x + 2], t->P[b + 1][y + 2][x + 2], t->P[b + 2][y + 2][x + 2], t->P[b + 3][y + 2][x + 2]};
+        return {t->p(b, y + 2, x + 2), t->p(b + 1, y + 2, x + 2), t->p(b + 2, y + 2, x + 2), t->p(b + 3, y + 2, x + 2)};
     }
 };
 
-template <class T, int TX, int TY>
-struct LdsInc {
-    const FusedTile<T, TX, TY>* t;
+template <class Tile>
+struct TileInc {
+    const Tile* t;
     int tau;
-    AF_HD T inc(int fam, int x, int y, int var) const {
-        return t->D[tau][fam * 3 + var][y + 1][x + 1];
-    }
+    AF_HD typename Tile::S inc(int fam, int x, int y, int var) const { return t->d(tau, fam * 3 + var, y + 1, x + 1); }
 };
+
+template <class T, int TX, int TY>
+using LdsAcc = TileAcc<FusedTile<T, TX, TY>>;
+template <class T, int TX, int TY>
+using LdsInc = TileInc<FusedTile<T, TX, TY>>;
 
 AF_HD int wrap_any(int v, int n) {
     v %= n;
