@@ -51,8 +51,8 @@ enum {
 enum { AF_F64 = 0, AF_F32 = 1 };
 
 enum {
-    AF_CHECK = 1,       /* af_step reads back the device status flag after each call
-                           (one host synchronisation per call) and returns the error */
+    AF_CHECK = 1,       /* af_step reads back the device status of every step (one host
+                           synchronisation per call and per 16 steps) and returns the error */
     AF_SCHEME_RB = 2,   /* additive RB point update (eq. barsukow-additive) instead of
                            the transported-increment update (eq. transported-update) */
     AF_SCHEME_FC = 4    /* foot-centred exact frozen-acoustic point update (App. C; Sec. 4,
@@ -113,9 +113,10 @@ af_status af_init(const af_config* cfg, void* hip_stream, af_ctx** out);
  * (eq. transported-update; density from the frozen invariant), space-time Simpson
  * fluxes and the conservative average update (eq. af-average-update).
  * inout: caller-owned device planes, overwritten with the state after nsteps.
- * Errors: AF_ERR_ARG for a bad dt (<= 0 or not finite); with AF_CHECK set, the
- * acoustic-CFL, foot and non-physical checks are read back after every step and, if
- * one fired, the call returns its status with *inout (and, for AF_F32, the context's
+ * Errors: AF_ERR_ARG for a bad dt (<= 0 or not finite); with AF_CHECK set, every
+ * step records its acoustic-CFL, foot and non-physical checks in a word of its own, read
+ * back every 16 steps and after the last; if one fired, the call returns the status of the
+ * first step that failed with *inout (and, for AF_F32, the context's
  * compensation planes) restored to the input of the call, whichever of the nsteps
  * steps failed.  The rollback copy is taken on the device before the first step
  * (allocated by the first such call).  Without AF_CHECK the flag is only accumulated

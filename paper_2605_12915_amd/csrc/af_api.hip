@@ -69,6 +69,11 @@ namespace {
 thread_local int g_last_hip = 0;
 
 constexpr int kDiagPartials = 4096;   // blocks of the first reduction pass
+// AF_CHECK: steps whose status words are read back together.  Every step has a word of its
+// own, so the first step that failed and its status are the same as with a read-back (a
+// copy and a host synchronisation, ~15 us) after each; a failure costs the steps enqueued
+// after it, at most kCheckSteps - 1.
+constexpr int kCheckSteps = 16;
 
 }  // namespace
 
@@ -81,7 +86,7 @@ struct af_ctx {
     void* state2 = nullptr;        // second state for ping-ponging (16 planes)
     void* state3 = nullptr;        // third state, only for af_time_steps
     void* scratch = nullptr;       // path scratch
-    unsigned* status = nullptr;    // device status bits
+    unsigned* status = nullptr;    // device status bits: kCheckSteps words, word 0 accumulates outside checked steps
     double* partials = nullptr;    // diagnostics partials
     double* diag_out = nullptr;    // af::kDiagVals doubles on the device
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};  // [0], [1] owned; [2], [3] per-launch timing slots
@@ -166,7 +171,7 @@ af_status status_from_bits(unsigned b) {
     return AF_OK;
 }
 
-hipError_t launch_step(af_ctx* c, void* const in[16], void* const out[16], double dt, bool timed) {
+hipError_t launch_step(af_ctx* c, void* const in[16], void* const out[16], double dt, bool timed, int word = 0) {
     af::StepArgs a;
     a.nx = c->cfg.nx;
     a.ny = c->cfg.ny;
@@ -176,7 +181,7 @@ hipError_t launch_step(af_ctx* c, void* const in[16], void* const out[16], doubl
     a.scheme = (c->cfg.flags & AF_SCHEME_RB) ? 1 : 0;
     for (int k = 0; k < 16; ++k) { a.in[k] = in[k]; a.out[k] = out[k]; }
     a.scratch = c->scratch;
-    a.status = c->status;
+    a.status = c->status + word;
     a.stream = c->stream;
     a.ev_begin = timed ? c->ev[2] : nullptr;
     a.ev_end = timed ? c->ev[3] : nullptr;
@@ -213,12 +218,14 @@ hipError_t ensure_snap(af_ctx* c) {
 
 void* snap_comp(af_ctx* c) { return (char*)c->snap + 16 * c->N * c->elem; }
 
-af_status read_status(af_ctx* c, unsigned* bits) {
-    unsigned h = 0;
-    AF_HIP(hipMemcpyAsync(&h, c->status, sizeof(unsigned), hipMemcpyDeviceToHost, c->stream));
+// Reads (and clears) the first `words` status words; *bits: the first that is not zero.
+af_status read_status(af_ctx* c, unsigned* bits, int words = 1) {
+    unsigned h[kCheckSteps] = {};
+    AF_HIP(hipMemcpyAsync(h, c->status, words * sizeof(unsigned), hipMemcpyDeviceToHost, c->stream));
     AF_HIP(hipStreamSynchronize(c->stream));
-    if (h) AF_HIP(hipMemsetAsync(c->status, 0, sizeof(unsigned), c->stream));
-    *bits = h;
+    *bits = 0;
+    for (int k = 0; k < words && !*bits; ++k) *bits = h[k];
+    if (*bits) AF_HIP(hipMemsetAsync(c->status, 0, words * sizeof(unsigned), c->stream));
     return AF_OK;
 }
 
@@ -486,11 +493,11 @@ af_status af_init(const af_config* cfg, void* hip_stream, af_ctx** out) {
     if (e == hipSuccess && c->variant == 2) e = af::prepare_split_f64();
     if (e == hipSuccess) e = hipMalloc(&c->state2, 16 * c->N * c->elem);
     if (e == hipSuccess) e = hipMalloc(&c->scratch, sbytes);
-    if (e == hipSuccess) e = hipMalloc((void**)&c->status, sizeof(unsigned));
+    if (e == hipSuccess) e = hipMalloc((void**)&c->status, kCheckSteps * sizeof(unsigned));
     if (e == hipSuccess) e = hipMalloc((void**)&c->partials, kDiagPartials * af::kDiagVals * sizeof(double));
     if (e == hipSuccess) e = hipMalloc((void**)&c->diag_out, af::kDiagVals * sizeof(double));
     for (int k = 0; k < 2 && e == hipSuccess; ++k) e = hipEventCreate(&c->ev[k]);
-    if (e == hipSuccess) e = hipMemsetAsync(c->status, 0, sizeof(unsigned), c->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(c->status, 0, kCheckSteps * sizeof(unsigned), c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) {
         g_last_hip = (int)e;
@@ -580,15 +587,16 @@ af_status af_step(af_ctx* c, af_state* inout, double dt, int32_t nsteps) {
     for (int s = 0; s < nsteps; ++s) {
         void** src = (s & 1) ? b : a;
         void** dst = (s & 1) ? a : b;
-        AF_HIP(launch_step(c, src, dst, dt, false));
-        if (check) {
+        const int word = check ? s % kCheckSteps : 0;
+        AF_HIP(launch_step(c, src, dst, dt, false, word));
+        if (check && (word == kCheckSteps - 1 || s == nsteps - 1)) {
             unsigned bits;
-            af_status st = read_status(c, &bits);
+            af_status st = read_status(c, &bits, word + 1);
             if (st != AF_OK) return st;
             if (bits) {
-                // *inout returns to the input of the call (step 0 writes the partner
-                // buffer only, so it is untouched when step 0 fails)
-                if (s > 0) AF_HIP(copy_state(c, a, snap));
+                // *inout returns to the input of the call (a single step writes the partner
+                // buffer only)
+                if (nsteps > 1) AF_HIP(copy_state(c, a, snap));
                 if (c->f32)
                     AF_HIP(hipMemcpyAsync(c->comp, snap_comp(c), 4 * c->N * sizeof(float), hipMemcpyDeviceToDevice,
                                           c->stream));
@@ -795,8 +803,8 @@ af_status af_init_batch(const af_config* cfgs, int32_t n, void* hip_stream, af_c
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking);
     for (int k = 0; k < 2 && e == hipSuccess; ++k) e = hipEventCreateWithFlags(&c->bev[k], hipEventDisableTiming);
     for (int k = 0; k < 2 && e == hipSuccess; ++k) e = hipEventCreate(&c->ev[k]);
-    if (e == hipSuccess) e = hipMalloc((void**)&c->status, sizeof(unsigned));
-    if (e == hipSuccess) e = hipMemsetAsync(c->status, 0, sizeof(unsigned), c->stream);
+    if (e == hipSuccess) e = hipMalloc((void**)&c->status, kCheckSteps * sizeof(unsigned));
+    if (e == hipSuccess) e = hipMemsetAsync(c->status, 0, kCheckSteps * sizeof(unsigned), c->stream);
     if (e == hipSuccess) e = hipMalloc((void**)&c->d_binst, n * sizeof(af::BatchInst));
     for (int q = 0; q < n && e == hipSuccess; ++q) {
         const af_config& cf = cfgs[q];
