@@ -29,7 +29,7 @@ CONTRACT_ON = {"af_fused_f32.hip", "af_fused_f32_small.hip", "af_batch.hip"}
 # Files whose LDS reads stay single: a ds_read2_b64 holds the LDS for 8.2 cycles, two
 # ds_read_b64 for 4.7 (16 waves per CU).  The FP32 31x10 and batch kernels are the faster with
 # paired reads, which cost them no LDS cycles and save issue slots.
-SINGLE_READS = {"af_fused.hip", "af_fused_f32_small.hip"}
+SINGLE_READS = {"af_adjoint.hip", "af_fused.hip", "af_fused_f32_small.hip"}
 
 
 # Backend options for the device code only (a plain -mllvm would also reach the host

@@ -310,153 +310,186 @@ AF_HD unsigned point_adj_target(const S_& S, const CT& cot1, const O_& O, int i,
     return out;
 }
 
-// Transposed 1-D Lagrange-to-monomial transform (see mono1): (lc0, lc1, lc2) -> (lf0, lf1, lf2).
-template <int XC, class T>
-AF_HD void mono1_T(T c0, T c1, T c2, T& f0, T& f1, T& f2) {
-    if constexpr (XC == 0) { f0 = c0 - T(3) * c1 + T(2) * c2; f1 = T(4) * c1 - T(4) * c2; f2 = -c1 + T(2) * c2; }
-    else if constexpr (XC == 1) { f0 = c1 + T(2) * c2; f1 = T(-4) * c1 - T(4) * c2; f2 = c0 + T(3) * c1 + T(2) * c2; }
-    else { f0 = -c1 + T(2) * c2; f1 = c0 - T(4) * c2; f2 = c1 + T(2) * c2; }
-}
-
-// Transposed wedge: adjoint of the accumulators -> adjoint of the cell's nodal (p, u, v),
-// scattered to the nodes of cell (ci, cj).
-template <int W, int XC, int YC, class T, class O_>
-AF_HD void wedge_adj(const T la[6][4], const O_& O, int ci, int cj) {
-    constexpr int RX = O_::kRX;
-    T lc[3][3][3];
-#pragma unroll
-    for (int v = 0; v < 3; ++v)
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) lc[v][a][b] = T(0);
-#pragma unroll
-    for (int al = 0; al < 3; ++al)
-#pragma unroll
-        for (int be = 0; be < 3; ++be) {
-            if (al + be == 0) continue;
-            const int m = al + be - 1;
-            const double* B = kBlk[W][al][be];
-            T sp = T(0), su = T(0), sv = T(0);
-            if (B[0] != 0.0) sp += T(B[0]) * la[0][m];
-            if (B[3] != 0.0) sp += T(B[3]) * la[2][m];
-            if (B[6] != 0.0) sp += T(B[6]) * la[4][m];
-            if (B[1] != 0.0) su += T(B[1]) * la[1][m];
-            if (B[4] != 0.0) su += T(B[4]) * la[3][m];
-            if (B[7] != 0.0) su += T(B[7]) * la[5][m];
-            if (B[2] != 0.0) sv += T(B[2]) * la[1][m];
-            if (B[5] != 0.0) sv += T(B[5]) * la[3][m];
-            if (B[8] != 0.0) sv += T(B[8]) * la[5][m];
-            lc[0][al][be] = sp;
-            lc[1][al][be] = su;
-            lc[2][al][be] = sv;
-        }
-    T lf[3][3][3];   // [var][x-node][y-node]
-#pragma unroll
-    for (int v = 0; v < 3; ++v) {
-        T lg[3][3];  // [alpha][y-node]
-#pragma unroll
-        for (int al = 0; al < 3; ++al) mono1_T<YC>(lc[v][al][0], lc[v][al][1], lc[v][al][2], lg[al][0], lg[al][1], lg[al][2]);
-#pragma unroll
-        for (int b = 0; b < 3; ++b) mono1_T<XC>(lg[0][b], lg[1][b], lg[2][b], lf[v][0][b], lf[v][1][b], lf[v][2][b]);
+// Transposed line transform (see line): coefficients' adjoint -> nodes' adjoint.
+template <int N, class T>
+AF_HD void line_T(const T* c, T* f) {
+    if constexpr (N == 5) {
+        const T e1 = T(4) * c[1] - T(2) * c[2], e2 = c[2] - c[1];
+        const T o1 = T(4) * c[3] - T(2) * c[4], o2 = c[4] - c[3];
+        f[0] = e2 - o2;
+        f[1] = e1 - o1;
+        f[2] = c[0] - T(2) * (e1 + e2);
+        f[3] = e1 + o1;
+        f[4] = e2 + o2;
+    } else {
+        f[0] = c[2] - c[1];
+        f[1] = c[0] - T(2) * c[2];
+        f[2] = c[2] + c[1];
     }
-    const int wb = O.base(ci, cj);
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            const int pl = win_plane(fam_of(a, b)), off = (b == 2 ? RX : 0) + (a == 2 ? 1 : 0);
-            O.addb(pl + 1, wb, off, lf[1][a][b]);
-            O.addb(pl + 2, wb, off, lf[2][a][b]);
-            O.addb(pl + 3, wb, off, lf[0][a][b]);
-        }
 }
 
-// Transposed node increments of node FAM at (i, j): Horner in r, freezing c_K and Z_K,
-// transposed monomial blocks and Lagrange-to-monomial transforms of every wedge.  A node
-// whose six increment cotangents are all zero contributes nothing and is skipped.
-template <int FAM, class T, class A_, class LD_, class O_>
+// Transposed block (see block_acc): adjoint of the sums -> adjoint of the coefficients
+// along y of variable VAR's coefficient A along x.
+template <int W, int NX, int NY, int VAR, int A, int B, int OUT, class T>
+AF_HD void block_term_T(const T (&la)[3][4], T (&c)[NY]) {
+    constexpr LineTerm x = LineTerms<NX>::t[A], y = LineTerms<NY>::t[B];
+    constexpr bool match = x.odd == ((OUT == 1) != (VAR == 1)) && y.odd == ((OUT == 2) != (VAR == 2));
+    if constexpr (match && x.pow + y.pow > 0) {
+        constexpr double w = kBlk[W][x.pow][y.pow][3 * OUT + VAR] * x.scale * y.scale;
+        if constexpr (w != 0.0) c[B] += T(w) * la[OUT][x.pow + y.pow - 1];
+    }
+}
+
+template <int W, int NX, int NY, int VAR, int A, class T, int... K>
+AF_HD void block_terms_T(const T (&la)[3][4], T (&c)[NY], std::integer_sequence<int, K...>) {
+    (block_term_T<W, NX, NY, VAR, A, K / 3, K % 3>(la, c), ...);
+}
+
+// One coefficient along x (A) of every row of the lines shared by a pair of families
+// (see pair_column), from the adjoint of both nodes' sums.
+template <int NX, int VAR, int A, class T>
+AF_HD void pair_column_T(const T (&la1)[3][4], const T (&la2)[3][4], T (&row)[5][NX]) {
+    constexpr int W1 = NX == 5 ? W_V_NE : W_EH_U, W2 = NX == 5 ? W_EV_R : W_C;
+    T c1[5] = {T(0), T(0), T(0), T(0), T(0)}, c2[3] = {T(0), T(0), T(0)}, f1[5], f2[3];
+    block_terms_T<W1, NX, 5, VAR, A>(la1, c1, std::make_integer_sequence<int, 15>());
+    block_terms_T<W2, NX, 3, VAR, A>(la2, c2, std::make_integer_sequence<int, 9>());
+    line_T<5>(c1, f1);
+    line_T<3>(c2, f2);
+#pragma unroll
+    for (int b = 0; b < 5; ++b) row[b][A] = b >= 2 ? f1[b] + f2[b - 2] : f1[b];
+}
+
+// Adjoint of the nodal values of one variable (0: p, 1: u, 2: v) from a pair's sums, each
+// node's share scattered once; own1, own2: what the two nodes themselves get besides.
+template <int NX, int VAR, class T, class O_>
+AF_HD void pair_scatter(const O_& O, int i, int j, const T (&la1)[3][4], const T (&la2)[3][4], T own1, T own2) {
+    constexpr int X0 = NX == 5 ? -2 : 0, MID = NX / 2;
+    T row[5][NX];
+    pair_column_T<NX, VAR, 0>(la1, la2, row);
+    pair_column_T<NX, VAR, 1>(la1, la2, row);
+    pair_column_T<NX, VAR, 2>(la1, la2, row);
+    if constexpr (NX == 5) {
+        pair_column_T<NX, VAR, 3>(la1, la2, row);
+        pair_column_T<NX, VAR, 4>(la1, la2, row);
+    }
+    const int wb = O.base(i, j);
+#pragma unroll
+    for (int b = 0; b < 5; ++b) {
+        T f[NX];
+        line_T<NX>(row[b], f);
+        if (b == 2) f[MID] += own1;
+        if (b == 3) f[MID] += own2;
+#pragma unroll
+        for (int a = 0; a < NX; ++a) {
+            const int x = X0 + a, y = b - 2;
+            const int fam = (x & 1) ? ((y & 1) ? F_C : F_EH) : ((y & 1) ? F_EV : F_V);
+            O.addb(win_plane(fam) + (VAR == 0 ? 3 : VAR), wb, (y - (y & 1)) / 2 * O_::kRX + (x - (x & 1)) / 2, f[a]);
+        }
+    }
+}
+
+// Transposed increments of one node: from the cotangents li of its increments and its
+// block sums (velocities' share auv in units of p / Z, pressure's share ap), the adjoint la
+// of the sums in units of p and those of the frozen c and Z.
+template <class T>
+AF_HD void node_adj(const T li[2][3], const T (&auv)[3][4], const T (&ap)[3][4], const Freeze<T>& z, T lam0, T lam1,
+                    T (&la)[3][4], T& lc, T& lZ) {
+    T a[3][4];
+#pragma unroll
+    for (int o = 0; o < 3; ++o)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) a[o][m] = z.Z * auv[o][m] + ap[o][m];
+    zero_acc(la);
+    T liZ = T(0);
+    lc = T(0);
+    lZ = T(0);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const T lam = t ? lam1 : lam0, r = z.c * lam;
+        // inc = (r / Z S_u, r / Z S_v, r S_pi), S_o = sum_m a[o][m] r^m; lq: adjoint of r S_o
+        const T lq[3] = {li[t][2], li[t][0] * z.iZ, li[t][1] * z.iZ};
+        T s[3], lr = T(0);
+#pragma unroll
+        for (int o = 0; o < 3; ++o) {
+            s[o] = ((a[o][3] * r + a[o][2]) * r + a[o][1]) * r + a[o][0];
+            const T ds = (T(3) * a[o][3] * r + T(2) * a[o][2]) * r + a[o][1];
+            lr += lq[o] * (s[o] + r * ds);
+            T w = lq[o] * r;
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                la[o][m] += w;
+                if (m < 3) w = w * r;
+            }
+        }
+        lc += lam * lr;
+        liZ += r * (li[t][0] * s[1] + li[t][1] * s[2]);
+    }
+    lZ = -z.iZ * z.iZ * liZ;
+#pragma unroll
+    for (int o = 0; o < 3; ++o)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) lZ += la[o][m] * auv[o][m];
+}
+
+// Transposed increments of a pair of families at cell (i, j) (NX as in pair_blocks).  The
+// lines and blocks are those of the forward operator transposed, so every node of the
+// stencil gets one contribution per pair and variable: 128 scattered additions per cell
+// for the two pairs, against 251 with one per wedge.  A node whose six increment
+// cotangents are all zero contributes nothing.
+template <int NX, class T, class A_, class LD_, class O_>
 AF_HD void incr_adj(const A_& A, const LD_& LD, const O_& O, int i, int j, T gamma, T lam0, T lam1) {
-    T li[2][3];
-    bool any = false;
+    constexpr int F1 = NX == 5 ? F_V : F_EH, F2 = NX == 5 ? F_EV : F_C;
+    T l1[2][3], l2[2][3];
+    bool any1 = false, any2 = false;
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
-            li[t][q] = LD.get(t * 12 + FAM * 3 + q, i, j);
-            any = any || (li[t][q] != T(0));
+            l1[t][q] = LD.get(t * 12 + F1 * 3 + q, i, j);
+            l2[t][q] = LD.get(t * 12 + F2 * 3 + q, i, j);
+            any1 = any1 || (l1[t][q] != T(0));
+            any2 = any2 || (l2[t][q] != T(0));
         }
-    if (!any) return;
-    const Prim<T> W = A.node(FAM, i, j);
-    // as in the forward freezing: 1 / Z = (gamma p rho)^(-1/2), c = gamma p / Z, Z = rho c
-    const T gp = gamma * W.p, q = gp * W.r;
-    const T iZ = rsqrt_of(q);
-    const T c = gp * iZ, Z = q * iZ;
-    NodeAcc<T> na;
-    na.zero();
-    node_wedges<FAM>(A, i, j, na);
-    T la[6][4];
-#pragma unroll
-    for (int ch = 0; ch < 6; ++ch)
-#pragma unroll
-        for (int m = 0; m < 4; ++m) la[ch][m] = T(0);
-    T lc = T(0), lZ = T(0), liZ = T(0);
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        const T lam = t ? lam1 : lam0;
-        const T r = c * lam;
-        T s[6], ds[6];
-#pragma unroll
-        for (int ch = 0; ch < 6; ++ch) {
-            s[ch] = ((na.a[ch][3] * r + na.a[ch][2]) * r + na.a[ch][1]) * r + na.a[ch][0];
-            ds[ch] = (T(3) * na.a[ch][3] * r + T(2) * na.a[ch][2]) * r + na.a[ch][1];
-        }
-        // inc0 = r (s2 iZ + s3), inc1 = r (s4 iZ + s5), inc2 = r (s0 + Z s1)
-        const T l0r = li[t][0] * r, l1r = li[t][1] * r, l2r = li[t][2] * r;
-        T ls[6];
-        ls[2] = l0r * iZ;
-        ls[3] = l0r;
-        ls[4] = l1r * iZ;
-        ls[5] = l1r;
-        ls[0] = l2r;
-        ls[1] = l2r * Z;
-        T rp = T(1);
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-#pragma unroll
-            for (int ch = 0; ch < 6; ++ch) la[ch][m] += ls[ch] * rp;
-            rp = rp * r;
-        }
-        const T lr = li[t][0] * (s[2] * iZ + s[3] + r * (ds[2] * iZ + ds[3])) +
-                     li[t][1] * (s[4] * iZ + s[5] + r * (ds[4] * iZ + ds[5])) +
-                     li[t][2] * (s[0] + Z * s[1] + r * (ds[0] + Z * ds[1]));
-        lc += lam * lr;
-        liZ += l0r * s[2] + l1r * s[4];
-        lZ += l2r * s[1];
-    }
-    lZ += -iZ * iZ * liZ;
+    if (!any1 && !any2) return;
+    T u1[3][4], u2[3][4], p1[3][4], p2[3][4];
+    zero_acc(u1);
+    zero_acc(u2);
+    pair_blocks<NX, true, true, 1>(A, i, j, u1, u2);
+    stage_fence(u1, u2);
+    pair_blocks<NX, true, true, 2>(A, i, j, u1, u2);
+    stage_fence(u1, u2);
+    zero_acc(p1);
+    zero_acc(p2);
+    pair_blocks<NX, true, true, 0>(A, i, j, p1, p2);
+    stage_fence(p1, p2);
+    const int wb = O.base(i, j);
+    T la1[3][4], la2[3][4], Z1 = T(0), Z2 = T(0), own1 = T(0), own2 = T(0);
+    zero_acc(la1);
+    zero_acc(la2);
     // c = sqrt(gamma p / rho), Z = rho c: dc/drho = -c / (2 rho) = -c^2 / (2 Z),
     // dc/dp = c / (2 p) = gamma / (2 Z), dZ/drho = c / 2, dZ/dp = Z / (2 p) = gamma rho / (2 Z)
-    {
-        const int wb = O.base(i, j);
-        const T hiZ = T(0.5) * iZ;
-        O.addb(win_plane(FAM), wb, 0, lc * (-c * c * hiZ) + lZ * (T(0.5) * c));
-        O.addb(win_plane(FAM) + 3, wb, 0, lc * (gamma * hiZ) + lZ * (gamma * W.r * hiZ));
-    }
-    if constexpr (FAM == F_V) {
-        wedge_adj<W_V_NE, 0, 0>(la, O, i, j);
-        wedge_adj<W_V_NW, 1, 0>(la, O, i - 1, j);
-        wedge_adj<W_V_SW, 1, 1>(la, O, i - 1, j - 1);
-        wedge_adj<W_V_SE, 0, 1>(la, O, i, j - 1);
-    } else if constexpr (FAM == F_EV) {
-        wedge_adj<W_EV_R, 0, 2>(la, O, i, j);
-        wedge_adj<W_EV_L, 1, 2>(la, O, i - 1, j);
-    } else if constexpr (FAM == F_EH) {
-        wedge_adj<W_EH_U, 2, 0>(la, O, i, j);
-        wedge_adj<W_EH_D, 2, 1>(la, O, i, j - 1);
-    } else {
-        wedge_adj<W_C, 2, 2>(la, O, i, j);
-    }
+    const PolAbs<T> pol{gamma, T(0)};
+    unsigned st = 0;
+    auto reduce = [&](int fam, const T (&li)[2][3], const T (&auv)[3][4], const T (&ap)[3][4], T (&la)[3][4], T& Z, T& own) {
+        const Prim<T> W = A.node(fam, i, j);
+        const Freeze<T> z = freeze_node(W, pol, lam1, st);
+        T lc, lZ;
+        node_adj(li, auv, ap, z, lam0, lam1, la, lc, lZ);
+        const T hiZ = T(0.5) * z.iZ;
+        O.addb(win_plane(fam), wb, 0, lc * (-z.c * z.c * hiZ) + lZ * (T(0.5) * z.c));
+        own = lc * (gamma * hiZ) + lZ * (gamma * W.r * hiZ);
+        Z = z.Z;
+    };
+    if (any1) reduce(F1, l1, u1, p1, la1, Z1, own1);
+    if (any2) reduce(F2, l2, u2, p2, la2, Z2, own2);
+    stage_fence(la1, la2);
+    pair_scatter<NX, 0>(O, i, j, la1, la2, own1, own2);
+    scale_acc(la1, Z1);
+    scale_acc(la2, Z2);
+    stage_fence(la1, la2);
+    pair_scatter<NX, 1>(O, i, j, la1, la2, T(0), T(0));
+    stage_fence(la1, la2);
+    pair_scatter<NX, 2>(O, i, j, la1, la2, T(0), T(0));
 }
 
 template <class T>

@@ -385,10 +385,8 @@ __global__ void __launch_bounds__(kIBX * kIBY, 2) k_adj_incr(StatePtrs<double> p
         const int j = j0 + (int)threadIdx.x / kIBX;
         if (i < nx && j < ny) {
             const PlanesAcc LD{lD, nx, ny};
-            incr_adj<F_V>(A, LD, O, i, j, gamma, lam0, lam1);
-            incr_adj<F_EV>(A, LD, O, i, j, gamma, lam0, lam1);
-            incr_adj<F_EH>(A, LD, O, i, j, gamma, lam0, lam1);
-            incr_adj<F_C>(A, LD, O, i, j, gamma, lam0, lam1);
+            incr_adj<5>(A, LD, O, i, j, gamma, lam0, lam1);
+            incr_adj<3>(A, LD, O, i, j, gamma, lam0, lam1);
         }
     }
     __syncthreads();

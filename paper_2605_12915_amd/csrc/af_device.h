@@ -118,77 +118,7 @@ AF_HD Prim<T> recover_centre(const T Ub[4], const Prim<T>& v00, const Prim<T>& v
 // ---------------------------------------------------------------------------
 // Exact node-centred acoustic operator (App. D)
 // ---------------------------------------------------------------------------
-// Monomial coefficients of the 1-D quadratic through (f0, f1, f2) at X0, X0+1/2,
-// X0+1 (units of h), written in differences so that constants give exact zeros.
-// XC = 0: X0 = 0;  XC = 1: X0 = -1;  XC = 2: X0 = -1/2.
-template <int XC, class T>
-AF_HD void mono1(T f0, T f1, T f2, T& c0, T& c1, T& c2) {
-    T d10 = f1 - f0, d20 = f2 - f0, d21 = f2 - f1;
-    c2 = T(2) * d20 - T(4) * d10;
-    if constexpr (XC == 0) { c0 = f0; c1 = T(4) * d10 - d20; }
-    else if constexpr (XC == 1) { c0 = f2; c1 = T(4) * d21 - d20; }
-    else { c0 = f1; c1 = d20; }
-}
-
-// Accumulators of one node: the r^m coefficient (m = 1..4) of
-//   [0] p-out from p-in, [1] p-out / Z from (u,v)-in, [2] u-out * Z from p-in,
-//   [3] u-out from (u,v)-in, [4] v-out * Z from p-in, [5] v-out from (u,v)-in.
-template <class T>
-struct NodeAcc {
-    T a[6][4];
-    AF_HD void zero() {
-#pragma unroll
-        for (int c = 0; c < 6; ++c)
-#pragma unroll
-            for (int m = 0; m < 4; ++m) a[c][m] = T(0);
-    }
-};
-
-// Add the contribution of wedge W (cell nodal data f[var][x-node][y-node] of
-// (p, u, v); the cell's lower-left node at (X0, Y0) relative to the node).
-template <int W, int XC, int YC, class T>
-AF_HD void wedge_acc(const T f[3][3][3], NodeAcc<T>& acc) {
-    T c[3][3][3];   // [var][alpha][beta]
-#pragma unroll
-    for (int v = 0; v < 3; ++v) {
-        T g[3][3];  // [alpha][y-node]
-#pragma unroll
-        for (int b = 0; b < 3; ++b) mono1<XC>(f[v][0][b], f[v][1][b], f[v][2][b], g[0][b], g[1][b], g[2][b]);
-#pragma unroll
-        for (int al = 0; al < 3; ++al) mono1<YC>(g[al][0], g[al][1], g[al][2], c[v][al][0], c[v][al][1], c[v][al][2]);
-    }
-#pragma unroll
-    for (int al = 0; al < 3; ++al)
-#pragma unroll
-        for (int be = 0; be < 3; ++be) {
-            if (al + be == 0) continue;
-            const int m = al + be - 1;
-            const double* B = kBlk[W][al][be];
-            const T cp = c[0][al][be], cu = c[1][al][be], cv = c[2][al][be];
-            if (B[0] != 0.0) acc.a[0][m] += T(B[0]) * cp;
-            if (B[1] != 0.0) acc.a[1][m] += T(B[1]) * cu;
-            if (B[2] != 0.0) acc.a[1][m] += T(B[2]) * cv;
-            if (B[3] != 0.0) acc.a[2][m] += T(B[3]) * cp;
-            if (B[4] != 0.0) acc.a[3][m] += T(B[4]) * cu;
-            if (B[5] != 0.0) acc.a[3][m] += T(B[5]) * cv;
-            if (B[6] != 0.0) acc.a[4][m] += T(B[6]) * cp;
-            if (B[7] != 0.0) acc.a[5][m] += T(B[7]) * cu;
-            if (B[8] != 0.0) acc.a[5][m] += T(B[8]) * cv;
-        }
-}
-
-// Increments (du, dv, dp) at radius r from the accumulators; Z = rho_K c_K.
-template <class T>
-AF_HD void node_increment(const NodeAcc<T>& A, T r, T Z, T iZ, T inc[3]) {
-    T s[6];
-#pragma unroll
-    for (int c = 0; c < 6; ++c) s[c] = ((A.a[c][3] * r + A.a[c][2]) * r + A.a[c][1]) * r + A.a[c][0];
-    inc[0] = r * (s[2] * iZ + s[3]);
-    inc[1] = r * (s[4] * iZ + s[5]);
-    inc[2] = r * (s[0] + Z * s[1]);
-}
-
-// The same operator in folded form.  The wedges of a node are mirror images of one
+// The compact monomial blocks in folded form.  The wedges of a node are mirror images of one
 // another, and so are their blocks (a factor -1 per odd power and per odd channel), so
 // the sum over them needs the data only in even and odd parts: along a line of five
 // nodes f at X = -1, -1/2, 0, 1/2, 1 about the node the monomial coefficients in |X| of

@@ -21,41 +21,6 @@ AF_HD void cell_nodes(const A& acc, int ci, int cj, Prim<T> n[3][3]) {
     n[0][2] = acc.node(F_V, ci, cj + 1);  n[1][2] = acc.node(F_EH, ci, cj + 1); n[2][2] = acc.node(F_V, ci + 1, cj + 1);
 }
 
-template <class T, class A>
-AF_HD void cell_puv(const A& acc, int ci, int cj, T f[3][3][3]) {
-    Prim<T> n[3][3];
-    cell_nodes<T>(acc, ci, cj, n);
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            f[0][a][b] = n[a][b].p;
-            f[1][a][b] = n[a][b].u;
-            f[2][a][b] = n[a][b].v;
-        }
-}
-
-// Accumulate every wedge of node family FAM at (i, j) (Sec. 3.1: four quadrants at
-// a vertex, two half-planes at an edge midpoint, the full disk at a centre).
-template <int FAM, class T, class A>
-AF_HD void node_wedges(const A& acc, int i, int j, NodeAcc<T>& na) {
-    T f[3][3][3];
-    if constexpr (FAM == F_V) {
-        cell_puv<T>(acc, i, j, f);         wedge_acc<W_V_NE, 0, 0>(f, na);
-        cell_puv<T>(acc, i - 1, j, f);     wedge_acc<W_V_NW, 1, 0>(f, na);
-        cell_puv<T>(acc, i - 1, j - 1, f); wedge_acc<W_V_SW, 1, 1>(f, na);
-        cell_puv<T>(acc, i, j - 1, f);     wedge_acc<W_V_SE, 0, 1>(f, na);
-    } else if constexpr (FAM == F_EV) {
-        cell_puv<T>(acc, i, j, f);         wedge_acc<W_EV_R, 0, 2>(f, na);
-        cell_puv<T>(acc, i - 1, j, f);     wedge_acc<W_EV_L, 1, 2>(f, na);
-    } else if constexpr (FAM == F_EH) {
-        cell_puv<T>(acc, i, j, f);         wedge_acc<W_EH_U, 2, 0>(f, na);
-        cell_puv<T>(acc, i, j - 1, f);     wedge_acc<W_EH_D, 2, 1>(f, na);
-    } else {
-        cell_puv<T>(acc, i, j, f);         wedge_acc<W_C, 2, 2>(f, na);
-    }
-}
-
 // Node freezing (Sec. 6.1 step 1): c_K, Z_K and 1 / Z_K.  Sets SB_CFL if c_K dt / h > 1/2
 // (lam1 = dt / h) and SB_NONPHYS if the node state is not physical.
 template <class T>

@@ -197,10 +197,8 @@ int main() {
     if (fix) std::fprintf(stderr, "warning: a counted target's Picard stages left one cell\n");
     const long adj_points = total() - a1;
     a1 = total();
-    incr_adj<F_V>(A, lD, O, 2, 2, gamma, lam0, lam1);
-    incr_adj<F_EV>(A, lD, O, 2, 2, gamma, lam0, lam1);
-    incr_adj<F_EH>(A, lD, O, 2, 2, gamma, lam0, lam1);
-    incr_adj<F_C>(A, lD, O, 2, 2, gamma, lam0, lam1);
+    incr_adj<5>(A, lD, O, 2, 2, gamma, lam0, lam1);
+    incr_adj<3>(A, lD, O, 2, 2, gamma, lam0, lam1);
     const long adj_incr = total() - a1;
     a1 = total();
     const Cnt lW[4] = {1e-2, 1e-2, 1e-2, 1e-2};
