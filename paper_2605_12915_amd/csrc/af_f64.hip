@@ -170,36 +170,39 @@ __global__ void __launch_bounds__(256) k_update(StatePtrs<double> in, const doub
     }
 }
 
-// Foot-centred exact point update (af_footcentred.h) of every target for both
-// durations: item e is duration e / 3N, family (e / N) mod 3, cell e mod N, so that
-// consecutive lanes take consecutive cells of one family and duration.  Registers
-// bounded for two workgroups per CU (2 waves per SIMD; 21% faster than the unbounded
-// allocation at one, 4x slower at four waves per SIMD, where it spills).
-__global__ void __launch_bounds__(256, 2) k_fc_points(StatePtrs<double> in, const double* C, double* half,
+// Foot-centred exact point update (af_footcentred.h): a half-wavefront per target of family
+// blockIdx.y mod 3 and duration blockIdx.y / 3, cells c0 + [0, count).  One thread per target,
+// with the radial integrals by 10 Gauss points, took 13.8 M FP64 flops per cell (20.1 ms on
+// 256^2; 7.2 ms on 96^2, whose 55296 threads left most of the chip idle); exact radial
+// integrals and 32 lanes per target 2.8 ms and 0.46 ms.  Bound by its arithmetic; three waves per
+// SIMD (168 registers) against two: 2.81 and 2.92 ms on 256^2, four spill 145 registers.
+constexpr int kFcGroups = 8;
+
+__global__ void __launch_bounds__(32 * kFcGroups, 3) k_fc_points(StatePtrs<double> in, const double* C, double* half,
                                                    StatePtrs<double> out, int nx, int ny, double gamma, double lam0,
-                                                   double lam1, unsigned* status) {
-    const size_t N = (size_t)nx * ny, total = 6 * N;
+                                                   double lam1, size_t c0, size_t count, unsigned* status) {
+    __shared__ FcShared sh[kFcGroups];
+    const size_t N = (size_t)nx * ny;
+    const int lane = threadIdx.x & 31, group = threadIdx.x >> 5, fam = blockIdx.y % 3;
+    const bool full = blockIdx.y >= 3;
+    const size_t e = (size_t)blockIdx.x * kFcGroups + group;
+    if (e >= count) return;
+    const size_t c = c0 + e;
+    unsigned st = 0;
     GAcc64 A{{}, C, nx, ny};
 #pragma unroll
     for (int k = 0; k < 16; ++k) A.s[k] = in.p[k];
-    unsigned st = 0;
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
-        const int tau = e >= 3 * N ? 1 : 0;
-        const size_t r = e - (size_t)tau * 3 * N;
-        const int fam = (int)(r / N);
-        const size_t c = r - (size_t)fam * N;
-        const int i = (int)(c % nx), j = (int)(c / nx);
-        const Prim<double> w = fc_point_update(A, fam, i, j, gamma, tau ? lam1 : lam0, st);
-        double* const q[4] = {tau ? out.p[4 + 4 * fam] : half + (size_t)(4 * fam) * N,
-                              tau ? out.p[5 + 4 * fam] : half + (size_t)(4 * fam + 1) * N,
-                              tau ? out.p[6 + 4 * fam] : half + (size_t)(4 * fam + 2) * N,
-                              tau ? out.p[7 + 4 * fam] : half + (size_t)(4 * fam + 3) * N};
-        q[0][c] = w.r;
-        q[1][c] = w.u;
-        q[2][c] = w.v;
-        q[3][c] = w.p;
+    const Prim<double> w = fc_point_group(A, fam, (int)(c % nx), (int)(c / nx), gamma, full ? lam1 : lam0, st, sh[group],
+                                          lane);
+    if (lane == 0) {
+        const double v[4] = {w.r, w.u, w.v, w.p};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            double* const o = fam == F_V ? out.p[4 + k] : (fam == F_EV ? out.p[8 + k] : out.p[12 + k]);
+            (full ? o : half + (size_t)(4 * fam + k) * N)[c] = v[k];
+        }
+        if (st) atomicOr(status, st);
     }
-    if (st) atomicOr(status, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -239,10 +242,14 @@ hipError_t launch_step_fc_f64(const StepArgs& a) {
     double* half = C + 4 * N;
     const double lam1 = a.dt / a.h, lam0 = 0.5 * lam1;
     hipLaunchKernelGGL(k_centre, grd, blk, 0, a.stream, in, C, a.nx, a.ny, a.gamma, a.status);
-    const size_t items = 6 * N, blocks = (items + 255) / 256;
     if (a.ev_begin) (void)hipEventRecord(a.ev_begin, a.stream);
-    hipLaunchKernelGGL(k_fc_points, dim3((unsigned)(blocks < (1u << 20) ? blocks : (1u << 20))), dim3(256), 0,
-                       a.stream, in, C, half, out, a.nx, a.ny, a.gamma, lam0, lam1, a.status);
+    // at most 2^26 cells a launch: 2^31 work-items along x
+    constexpr size_t kChunk = size_t(1) << 26;
+    for (size_t c0 = 0; c0 < N; c0 += kChunk) {
+        const size_t count = N - c0 < kChunk ? N - c0 : kChunk;
+        hipLaunchKernelGGL(k_fc_points, dim3((unsigned)((count + kFcGroups - 1) / kFcGroups), 6), dim3(32 * kFcGroups), 0,
+                           a.stream, in, C, half, out, a.nx, a.ny, a.gamma, lam0, lam1, c0, count, a.status);
+    }
     if (a.ev_end) (void)hipEventRecord(a.ev_end, a.stream);
     hipLaunchKernelGGL(k_update, grd, blk, 0, a.stream, in, half, out, a.nx, a.ny, a.gamma, lam1);
     return hipGetLastError();

@@ -23,9 +23,16 @@
 // graded towards the tangency) and where a ray passes through a grid corner, and each
 // ray's psi range split where it crosses a grid line, so that every piece lies in one
 // cell; 32 Gauss points per angular piece, clustered towards both ends by
-// theta = t0 + (t1 - t0)(1 - cos(pi s)) / 2 (square-root behaviour at a tangency), and
-// 10 per radial piece.  The footprint keeps the disk inside the 2 x 2 cells around P,
-// so at most one vertical and one horizontal grid line cut it.
+// theta = t0 + (t1 - t0)(1 - cos(pi s)) / 2 (square-root behaviour at a tangency).  Along a
+// ray's piece the integrands are polynomials in |z| (the Q2 data of one cell), so the
+// radial integrals are exact sums of the moments of sin(psi)^k.  The footprint keeps the
+// disk inside the 2 x 2 cells around P, so at most one vertical and one horizontal grid line
+// cut it.
+//
+// On the device one half-wavefront takes a target and duration (fc_point_group): a lane
+// computes one of the (at most 25) cuts, which are sorted across the lanes, loads one of the
+// 25 lattice nodes, and is one of the 32 angular nodes of every piece.  The host build runs
+// the same pieces and nodes one after the other.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -37,169 +44,241 @@ namespace af {
 
 constexpr double kFcPi = 3.14159265358979323846;
 
-// Nodal values of one cell, minus the frozen values: p, u, v at [a][b] (a along x).
-struct FcCell { double p[3][3], u[3][3], v[3][3]; };
+// Polynomials of one cell about the foot in the unit disk's coordinates z (offsets divided
+// by R), from the nodal values minus the frozen state: p[a][b] of z_x^a z_y^b, and R times
+// the divergence g = du/dx + dv/dy, whose coefficients combine along a ray with
+// (c, s) = (cos, sin): g0, g1c c + g1s s, g2cc c^2 + g2cs c s + g2ss s^2, g3css c s^2 + g3ccs c^2 s.
+struct FcPoly { double p[3][3], g0, g1c, g1s, g2cc, g2cs, g2ss, g3css, g3ccs; };
 
-// Quadrature sums over the disk: M_R of (p - p*), z . grad p, g, grad p; history
-// (1 / 2 pi) int int g e_theta dpsi dtheta.
-struct FcSums { double m0, m1, mg, mx, my, hx, hy; };
+// Sums over the disk, from which the point value follows: m = M_R[p - p*] + R M_R[z . grad p],
+// and R times M_R[g], M_R[grad p] and the history term (1 / 2 pi) int int g e_theta dpsi dtheta.
+struct FcSums { double m, g, x, y, hx, hy; };
 
-AF_HD void fc_lagrange(double s, double L[3], double dL[3]) {
-    // Lagrange basis at s = -1, 0, 1 and its derivative in cell units (d/dX = 2 d/ds)
-    L[0] = 0.5 * s * (s - 1.0);
-    L[1] = 1.0 - s * s;
-    L[2] = 0.5 * s * (s + 1.0);
-    dL[0] = 2.0 * s - 1.0;
-    dL[1] = -4.0 * s;
-    dL[2] = 2.0 * s + 1.0;
+// Coefficients of z^k of the quadratic through f at 0, 1/2, 1, about x, scaled by R.
+AF_HD void fc_shift(double f0, double f1, double f2, double x, double R, double c[3]) {
+    const double d1 = f1 - f0, d2 = f2 - f0, a = 4.0 * d1 - d2, b = 2.0 * d2 - 4.0 * d1;
+    c[0] = f0 + x * (a + b * x);
+    c[1] = R * (a + 2.0 * b * x);
+    c[2] = R * R * b;
 }
 
-// Add one quadrature point (local coordinates s, t in the cell; unit-disk position z;
-// weights w of M_R and wh of the history term).
-AF_HD void fc_point(const FcCell& c, double s, double t, double zx, double zy, double ct,
-                                         double st, double w, double wh, FcSums& S) {
-    double Lx[3], dLx[3], Ly[3], dLy[3];
-    fc_lagrange(s, Lx, dLx);
-    fc_lagrange(t, Ly, dLy);
-    double p0 = 0.0, px = 0.0, py = 0.0, ux = 0.0, vy = 0.0;
+// n(var, a, b): nodal value (0: p, 1: u, 2: v) [x-node][y-node] of the cell whose lower left
+// corner is (x0, y0) from the foot.
+template <class N>
+AF_HD void fc_poly(const N& n, double x0, double y0, double R, FcPoly& c) {
+    double k[3][3][3];
 #pragma unroll
-    for (int b = 0; b < 3; ++b) {
-        const double r = Lx[0] * c.p[0][b] + Lx[1] * c.p[1][b] + Lx[2] * c.p[2][b];
-        const double rd = dLx[0] * c.p[0][b] + dLx[1] * c.p[1][b] + dLx[2] * c.p[2][b];
-        const double ud = dLx[0] * c.u[0][b] + dLx[1] * c.u[1][b] + dLx[2] * c.u[2][b];
-        p0 += Ly[b] * r;
-        px += Ly[b] * rd;
-        py += dLy[b] * r;
-        ux += Ly[b] * ud;
+    for (int v = 0; v < 3; ++v) {
+        double row[3][3];
+#pragma unroll
+        for (int b = 0; b < 3; ++b) fc_shift(n(v, 0, b), n(v, 1, b), n(v, 2, b), -x0, R, row[b]);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) fc_shift(row[0][a], row[1][a], row[2][a], -y0, R, k[v][a]);
     }
 #pragma unroll
-    for (int a = 0; a < 3; ++a) vy += Lx[a] * (dLy[0] * c.v[a][0] + dLy[1] * c.v[a][1] + dLy[2] * c.v[a][2]);
-    const double g = ux + vy;
-    S.m0 += w * p0;
-    S.m1 += w * (zx * px + zy * py);
-    S.mg += w * g;
-    S.mx += w * px;
-    S.my += w * py;
-    S.hx += wh * g * ct;
-    S.hy += wh * g * st;
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) c.p[a][b] = k[0][a][b];
+    const double(&u)[3][3] = k[1];
+    const double(&w)[3][3] = k[2];
+    c.g0 = u[1][0] + w[0][1];
+    c.g1c = 2.0 * u[2][0] + w[1][1];
+    c.g1s = u[1][1] + 2.0 * w[0][2];
+    c.g2cc = w[2][1];
+    c.g2cs = 2.0 * (u[2][1] + w[1][2]);
+    c.g2ss = u[1][2];
+    c.g3css = 2.0 * u[2][2];
+    c.g3ccs = 2.0 * w[2][2];
 }
 
-// Sort a short array in place (insertion sort).
-AF_HD void fc_sort(double* a, int n) {
-    for (int k = 1; k < n; ++k) {
-        const double v = a[k];
-        int m = k - 1;
-        while (m >= 0 && a[m] > v) { a[m + 1] = a[m]; --m; }
-        a[m + 1] = v;
-    }
+// The disk about the foot (X, Y) (relative to the target's cell, cell units) of radius R,
+// 0 < R, |X - ox| + R < 1/2, |Y - oy| + R < 1/2, and the grid lines that cut it: at most one
+// in each direction, at lam, mu (units of R).
+struct FcDisk {
+    double X, Y, R, lam, mu;
+    int kx, ky;
+    bool hx, hy;
+};
+
+AF_HD FcDisk fc_disk_of(double X, double Y, double R) {
+    FcDisk d;
+    d.X = X; d.Y = Y; d.R = R;
+    d.kx = (int)floor(X + R);
+    d.ky = (int)floor(Y + R);
+    d.hx = (double)d.kx > X - R && (double)d.kx < X + R;
+    d.hy = (double)d.ky > Y - R && (double)d.ky < Y + R;
+    d.lam = d.hx ? ((double)d.kx - X) / R : 0.0;
+    d.mu = d.hy ? ((double)d.ky - Y) / R : 0.0;
+    return d;
 }
 
-// The disk sums for the foot at (Xf, Yf) relative to the target's cell (i, j) (cell
-// units) and radius R, 0 < R, |Xf - ox| + R < 1/2, |Yf - oy| + R < 1/2.  ws: frozen
-// state, subtracted from the nodal values (uniform data give zero sums exactly).
-template <class A>
-AF_HD void fc_disk(const A& acc, int i, int j, double Xf, double Yf, double R, const Prim<double>& ws,
-                        FcSums& S) {
-    S = FcSums{0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    // the grid lines that cut the disk: at most one in each direction
-    const int kx = (int)floor(Xf + R), ky = (int)floor(Yf + R);
-    const bool hx = (double)kx > Xf - R && (double)kx < Xf + R;
-    const bool hy = (double)ky > Yf - R && (double)ky < Yf + R;
-    const double lam = hx ? ((double)kx - Xf) / R : 0.0, mu = hy ? ((double)ky - Yf) / R : 0.0;
-    double cuts[32];
-    int nc = 0;
-    for (int q = 0; q < 8; ++q) cuts[nc++] = q * (0.25 * kFcPi);
-    auto tangency = [&](double l, double base) {
-        const double a = acos(fmin(1.0, fabs(l)));
-        cuts[nc++] = base - a;
-        cuts[nc++] = base + a;
-        const double gr[3] = {0.25, 1.0, 4.0};
-        for (int q = 0; q < 3; ++q) {
-            const double d = gr[q] * fabs(l);
-            if (d < a) {
-                cuts[nc++] = base - a + d;
-                cuts[nc++] = base + a - d;
-            }
-        }
-    };
-    if (hx) tangency(lam, lam > 0.0 ? 0.0 : kFcPi);
-    if (hy) tangency(mu, mu > 0.0 ? 0.5 * kFcPi : 1.5 * kFcPi);
-    if (hx && hy) {
-        const double dx = (double)kx - Xf, dy = (double)ky - Yf;
-        if (dx * dx + dy * dy < R * R) cuts[nc++] = atan2(dy, dx);
+constexpr int kFcCuts = 25;   // candidates for a cut of the angle, fc_cut(d, 0 .. kFcCuts - 1)
+
+// Candidate q for a cut, in [0, 2 pi]; 2 pi where there is none.
+AF_HD double fc_cut(const FcDisk& d, int q) {
+    constexpr double full = 2.0 * kFcPi;
+    double c = full;
+    if (q < 8) return q * (0.25 * kFcPi);
+    if (q < 24) {
+        // tangencies of the vertical (8 .. 15) and the horizontal line (16 .. 23): the two
+        // angles, then cuts graded towards them
+        const bool vert = q < 16;
+        const double l = vert ? d.lam : d.mu;
+        if (!(vert ? d.hx : d.hy)) return full;
+        const double base = (vert ? 0.0 : 0.5 * kFcPi) + (l > 0.0 ? 0.0 : kFcPi), a = acos(fmin(1.0, fabs(l)));
+        const int g = (q & 7) >> 1;
+        const double gr = g == 0 ? 0.0 : (g == 1 ? 0.25 : (g == 2 ? 1.0 : 4.0)), t = gr * fabs(l);
+        if (g > 0 && !(t < a)) return full;
+        c = (q & 1) ? base + a - t : base - a + t;
+    } else {
+        if (!(d.hx && d.hy)) return full;
+        const double dx = (double)d.kx - d.X, dy = (double)d.ky - d.Y;
+        if (!(dx * dx + dy * dy < d.R * d.R)) return full;
+        c = atan2(dy, dx);
     }
-    for (int q = 0; q < nc; ++q) {
-        double c = fmod(cuts[q], 2.0 * kFcPi);
-        if (c < 0.0) c += 2.0 * kFcPi;
-        cuts[q] = c;
+    if (c < 0.0) c += full;
+    if (c >= full) c -= full;
+    return c;
+}
+
+// cos and sin of tm + d for |d| <= pi/8 + rounding, from those of tm: the Taylor series of
+// cos d - 1 and sin d (terms left out below 1e-17 at 0.4) and the addition theorem.
+AF_HD void fc_turn(double cm, double sm, double d, double& c, double& s) {
+    const double x = d * d;
+    double sd = -1.0 / 1307674368000.0;                 // -1/15!
+    sd = fma(sd, x, 1.0 / 6227020800.0);
+    sd = fma(sd, x, -1.0 / 39916800.0);
+    sd = fma(sd, x, 1.0 / 362880.0);
+    sd = fma(sd, x, -1.0 / 5040.0);
+    sd = fma(sd, x, 1.0 / 120.0);
+    sd = fma(sd, x, -1.0 / 6.0);
+    sd = fma(sd * x, d, d);
+    double cd = 1.0 / 20922789888000.0;                 // 1/16!
+    cd = fma(cd, x, -1.0 / 87178291200.0);
+    cd = fma(cd, x, 1.0 / 479001600.0);
+    cd = fma(cd, x, -1.0 / 3628800.0);
+    cd = fma(cd, x, 1.0 / 40320.0);
+    cd = fma(cd, x, -1.0 / 720.0);
+    cd = fma(cd, x, 1.0 / 24.0);
+    cd = fma(cd, x, -0.5) * x;                          // cos d - 1
+    c = cm + (cm * cd - sm * sd);
+    s = sm + (sm * cd + cm * sd);
+}
+
+// cos and sin of an angle in [0, 2 pi], turned from the nearest multiple of pi/4.
+AF_HD void fc_angle(double t, double& c, double& s) {
+    constexpr double h = 0.70710678118654752440, lo = 3.061616997868383e-17;   // pi/4 - (double)(pi/4)
+    const double m = floor(t * (4.0 / kFcPi) + 0.5);
+    const int q = (int)m & 7, r = q & 3;
+    const double a = r == 0 ? 1.0 : (r == 2 ? 0.0 : (r == 1 ? h : -h)), b = r == 0 ? 0.0 : (r == 2 ? 1.0 : h);
+    fc_turn(q < 4 ? a : -a, q < 4 ? b : -b, fma(-m, 0.25 * kFcPi, t) - m * lo, c, s);
+}
+
+// One angular piece [t0, t0 + dt]: cos and sin of its middle, and a code of the lines that its
+// rays cross in the order of increasing radius (the same for every ray of the piece): bits
+// 0-1 their number, bit 2 set if the horizontal line comes first, bits 4-5, 6-7 and 8-9 the cells
+// of the radial pieces as indices into the 2 x 2 cells around (kx, ky), 2 (upper row) +
+// (right column).
+struct FcPiece { double dt, cm, sm; int code; };
+
+AF_HD FcPiece fc_piece(const FcDisk& d, double t0, double t1) {
+    FcPiece w;
+    w.dt = t1 - t0;
+    const double tm = 0.5 * (t0 + t1);
+    fc_angle(tm, w.cm, w.sm);
+    const double qx = d.lam / w.cm, qy = d.mu / w.sm;
+    const bool cx = d.hx && qx > 0.0 && qx < 1.0, cy = d.hy && qy > 0.0 && qy < 1.0;
+    const int n = (cx ? 1 : 0) + (cy ? 1 : 0);
+    const bool yfirst = cy && (!cx || qy < qx);
+    const double q0 = n == 0 ? 1.0 : (yfirst ? qy : qx), q1 = n < 2 ? 1.0 : (yfirst ? qx : qy);
+    const double q[4] = {0.0, q0, q1, 1.0};
+    w.code = n + (yfirst ? 4 : 0);
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+        // the middle (in radius) of the radial piece on the middle ray
+        const double r = 0.5 * (q[s] + q[s + 1]);
+        const int ix = (int)floor(d.X + d.R * r * w.cm) - (d.kx - 1), iy = (int)floor(d.Y + d.R * r * w.sm) - (d.ky - 1);
+        w.code += (2 * (iy > 0 ? 1 : 0) + (ix > 0 ? 1 : 0)) << (4 + 2 * s);
     }
-    cuts[nc++] = 2.0 * kFcPi;
-    fc_sort(cuts, nc);
-    const double inv2pi = 1.0 / (2.0 * kFcPi);
-    for (int q = 0; q + 1 < nc; ++q) {
-        const double t0 = cuts[q], t1 = cuts[q + 1];
-        if (t1 - t0 < 1e-15) continue;
-        // lines crossed by the rays of this piece, in the order of increasing radius
-        // (the same for every ray of the piece)
-        const double tm = 0.5 * (t0 + t1), cm = cos(tm), sm = sin(tm);
-        int nx_ = 0;
-        int axis[2];
-        double qm[2];
-        if (hx && lam / cm > 0.0 && lam / cm < 1.0) { axis[nx_] = 0; qm[nx_] = lam / cm; ++nx_; }
-        if (hy && mu / sm > 0.0 && mu / sm < 1.0) { axis[nx_] = 1; qm[nx_] = mu / sm; ++nx_; }
-        if (nx_ == 2 && qm[1] < qm[0]) {
-            const int a = axis[0]; axis[0] = axis[1]; axis[1] = a;
-            const double b = qm[0]; qm[0] = qm[1]; qm[1] = b;
-        }
-        for (int seg = 0; seg <= nx_; ++seg) {
-            // this radial piece's cell, from its middle on the middle ray
-            const double p0m = seg == 0 ? 0.0 : asin(qm[seg - 1]);
-            const double p1m = seg == nx_ ? 0.5 * kFcPi : asin(qm[seg]);
-            const double rm = sin(0.5 * (p0m + p1m));
-            const int cx = (int)floor(Xf + R * rm * cm), cy = (int)floor(Yf + R * rm * sm);
-            FcCell C;
-            {
-                Prim<double> n[3][3];
-                cell_nodes<double>(acc, i + cx, j + cy, n);
+    return w;
+}
+
+// Antiderivatives at psi (s = sin psi, c = cos psi) of sin^k, k = 0 .. 5.
+struct FcMom { double v[6]; };
+
+AF_HD FcMom fc_moments(double psi, double s, double c) {
+    FcMom m;
+    m.v[0] = psi;
+    m.v[1] = -c;
+    double e = s;
 #pragma unroll
-                for (int a = 0; a < 3; ++a)
+    for (int k = 2; k < 6; ++k) {
+        m.v[k] = ((k - 1) * m.v[k - 2] - e * c) * (1.0 / k);
+        e *= s;
+    }
+    return m;
+}
+
+// The radial piece between the moments lo and hi on the ray (c, s), weight w, in one cell.
+AF_HD void fc_ray(const FcPoly& P, double c, double s, double w, const FcMom& lo, const FcMom& hi, FcSums& S) {
+    double I[6];
 #pragma unroll
-                    for (int b = 0; b < 3; ++b) {
-                        C.p[a][b] = n[a][b].p - ws.p;
-                        C.u[a][b] = n[a][b].u - ws.u;
-                        C.v[a][b] = n[a][b].v - ws.v;
-                    }
-            }
+    for (int k = 0; k < 6; ++k) I[k] = w * (hi.v[k] - lo.v[k]);
+    const double cc = c * c, cs = c * s, ss = s * s;
+    // R grad p along the ray by powers of |z|, and R g
+    const double x[4] = {P.p[1][0], 2.0 * P.p[2][0] * c + P.p[1][1] * s, 2.0 * P.p[2][1] * cs + P.p[1][2] * ss,
+                         2.0 * P.p[2][2] * c * ss};
+    const double y[4] = {P.p[0][1], P.p[1][1] * c + 2.0 * P.p[0][2] * s, P.p[2][1] * cc + 2.0 * P.p[1][2] * cs,
+                         2.0 * P.p[2][2] * cc * s};
+    const double g[4] = {P.g0, P.g1c * c + P.g1s * s, P.g2cc * cc + P.g2cs * cs + P.g2ss * ss,
+                         P.g3css * c * ss + P.g3ccs * cc * s};
+    double m = P.p[0][0] * I[1], gm = 0.0, xm = 0.0, ym = 0.0, hm = 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        // p's coefficient of |z|^(k+1) is (c x_k + s y_k) / (k + 1); z . grad p has k + 1 times it
+        m += (c * x[k] + s * y[k]) * ((1.0 + 1.0 / (k + 1)) * I[k + 2]);
+        gm += g[k] * I[k + 1];
+        xm += x[k] * I[k + 1];
+        ym += y[k] * I[k + 1];
+        hm += g[k] * I[k];
+    }
+    S.m += m;
+    S.g += gm;
+    S.x += xm;
+    S.y += ym;
+    S.hx += hm * c;
+    S.hy += hm * s;
+}
+
+// Angular node (position xc = cos(pi x), weight wt = w pi sin(pi x) / 2 of the clustered rule)
+// of a piece: every radial piece of its ray.  poly(cell): the cell's polynomials.
+template <class P>
+AF_HD void fc_node(const FcDisk& d, const FcPiece& w, double xc, double wt, const P& poly, FcSums& S) {
+    double c, s;
+    fc_turn(w.cm, w.sm, -0.5 * w.dt * xc, c, s);
+    const double wk = wt * w.dt * (1.0 / (2.0 * kFcPi));
+    const int n = w.code & 3;
+    FcMom lo = fc_moments(0.0, 0.0, 1.0);
 #pragma unroll 1
-            for (int k = 0; k < 32; ++k) {
-                const double th = t0 + 0.5 * (t1 - t0) * (1.0 - kGaussCos32[k]);
-                const double wth = kGaussW32[k] * 0.5 * (t1 - t0) * kFcPi * kGaussSin32[k];
-                const double ct = cos(th), st = sin(th);
-                auto psi_at = [&](int c) -> double {
-                    const double qv = axis[c] == 0 ? lam / ct : mu / st;
-                    return asin(fmin(1.0, fmax(0.0, qv)));
-                };
-                const double p0 = seg == 0 ? 0.0 : psi_at(seg - 1);
-                const double p1 = seg == nx_ ? 0.5 * kFcPi : psi_at(seg);
-                const bool whole = nx_ == 0;   // psi over [0, pi/2]: tabulated sines
-#pragma unroll 2
-                for (int m = 0; m < 10; ++m) {
-                    const double wps = (p1 - p0) * kGaussW10[m];
-                    const double rho = whole ? kGaussSinHalf10[m] : sin(p0 + (p1 - p0) * kGaussX10[m]);
-                    const double zx = rho * ct, zy = rho * st;
-                    const double X = Xf + R * zx, Y = Yf + R * zy;
-                    fc_point(C, 2.0 * (X - cx) - 1.0, 2.0 * (Y - cy) - 1.0, zx, zy, ct, st,
-                             wth * wps * rho * inv2pi, wth * wps * inv2pi, S);
-                }
-            }
+    for (int q = 0; q <= n; ++q) {
+        double psi = 0.5 * kFcPi, sp = 1.0, cp = 0.0;   // the ray's end
+        if (q < n) {
+            const bool horizontal = ((w.code >> 2) & 1) != q;
+            sp = fmin(1.0, fmax(0.0, (horizontal ? d.mu : d.lam) / (horizontal ? s : c)));
+            psi = asin(sp);
+            cp = sqrt((1.0 - sp) * (1.0 + sp));
         }
+        const FcMom hi = fc_moments(psi, sp, cp);
+        fc_ray(poly((w.code >> (4 + 2 * q)) & 3), c, s, wk, lo, hi, S);
+        lo = hi;
     }
 }
 
-// New point value of the target of family fam at (i, j) after tau = lam h.
+// What precedes the disk: foot, frozen state, radius and the footprint check.  Returns false
+// where the value is ws as it stands.
 template <class A>
-AF_HD Prim<double> fc_point_update(const A& acc, int fam, int i, int j, double gamma, double lam,
-                                        unsigned& st) {
+AF_HD bool fc_foot(const A& acc, int fam, int i, int j, double gamma, double lam, unsigned& st, Prim<double>& ws,
+                   double& c2, FcDisk& d) {
     const PolAbs<double> pol{gamma, 1.0 / (gamma - 1.0)};
     const Prim<double> WP = acc.node(fam, i, j);
     int ci, cj;
@@ -207,38 +286,147 @@ AF_HD Prim<double> fc_point_update(const A& acc, int fam, int i, int j, double g
     picard_foot(acc, fam, i, j, pol, lam, WP, ci, cj, xi, eta, st);
     lag_pm(xi, xm, xp);
     lag_pm(eta, ym, yp);
-    double fr[3][3], fu[3][3], fv[3][3], fp[3][3];
-    {
-        Prim<double> n[3][3];
-        cell_nodes<double>(acc, ci, cj, n);
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                fr[a][b] = n[a][b].r; fu[a][b] = n[a][b].u; fv[a][b] = n[a][b].v; fp[a][b] = n[a][b].p;
-            }
-    }
-    const Prim<double> ws{q2(xm, xp, ym, yp, fr), q2(xm, xp, ym, yp, fu), q2(xm, xp, ym, yp, fv),
-                          q2(xm, xp, ym, yp, fp)};
+    double f[3][3];
+    cell_field<3>(acc, ci, cj, f);
+    ws.r = q2(xm, xp, ym, yp, f);
+    cell_field<1>(acc, ci, cj, f);
+    ws.u = q2(xm, xp, ym, yp, f);
+    cell_field<2>(acc, ci, cj, f);
+    ws.v = q2(xm, xp, ym, yp, f);
+    cell_field<0>(acc, ci, cj, f);
+    ws.p = q2(xm, xp, ym, yp, f);
     if (!(ws.r > 0.0) || !(ws.p > 0.0)) {
         st |= SB_NONPHYS;
-        return ws;
+        return false;
     }
-    const double c2 = gamma * ws.p / ws.r, c = sqrt(c2), Z = ws.r * c, R = c * lam;
+    c2 = gamma * ws.p / ws.r;
+    const double R = sqrt(c2) * lam;
     // foot relative to the target's cell, and its displacement from the target
     const double Xf = (double)(ci - i) + 0.5 * (xi + 1.0), Yf = (double)(cj - j) + 0.5 * (eta + 1.0);
     const double dx = Xf - fam_ox<double>(fam), dy = Yf - fam_oy<double>(fam);
     if (!(fabs(dx) + R < 0.5) || !(fabs(dy) + R < 0.5)) {
         st |= SB_FOOTPRINT;
-        return ws;
+        return false;
     }
-    if (!(R > 0.0)) return ws;
-    FcSums S;
-    fc_disk(acc, i, j, Xf, Yf, R, ws, S);
-    const double p = ws.p + S.m0 + R * S.m1 - Z * R * S.mg;
-    const double u = ws.u - (R / Z) * S.mx + R * S.hx;
-    const double v = ws.v - (R / Z) * S.my + R * S.hy;
-    return Prim<double>{ws.r + (p - ws.p) / c2, u, v, p};
+    if (!(R > 0.0)) return false;
+    d = fc_disk_of(Xf, Yf, R);
+    return true;
 }
+
+AF_HD Prim<double> fc_value(const Prim<double>& ws, double c2, const FcSums& S) {
+    const double Z = ws.r * sqrt(c2);
+    const double p = ws.p + S.m - Z * S.g;
+    return Prim<double>{ws.r + (p - ws.p) / c2, ws.u - S.x / Z + S.hx, ws.v - S.y / Z + S.hy, p};
+}
+
+// Lattice node n (0 .. 24) of the 2 x 2 cells around (kx, ky): half cells (n % 5, n / 5) from the
+// vertex of cell (kx - 1, ky - 1).
+template <class A>
+AF_HD Prim<double> fc_lattice(const A& acc, const FcDisk& d, int i, int j, int n) {
+    const int a = n % 5, b = n / 5;
+    const int fam = (a & 1) ? ((b & 1) ? F_C : F_EH) : ((b & 1) ? F_EV : F_V);
+    return acc.node(fam, i + d.kx - 1 + a / 2, j + d.ky - 1 + b / 2);
+}
+
+// Polynomials of cell q (0 .. 3) of the 2 x 2, from the lattice's values nd[3][25] (p, u, v) minus
+// the frozen state.
+AF_HD void fc_cell_poly(const FcDisk& d, const double* nd, int q, FcPoly& P) {
+    const int cx = q & 1, cy = q >> 1;
+    fc_poly([&](int v, int a, int b) { return nd[v * 25 + (2 * cy + b) * 5 + 2 * cx + a]; }, (double)(d.kx - 1 + cx) - d.X,
+            (double)(d.ky - 1 + cy) - d.Y, d.R, P);
+}
+
+// New point value of the target of family fam at (i, j) after tau = lam h, one piece and
+// node after the other (host build).
+template <class A>
+AF_HD Prim<double> fc_point_update(const A& acc, int fam, int i, int j, double gamma, double lam, unsigned& st) {
+    Prim<double> ws;
+    double c2;
+    FcDisk d;
+    if (!fc_foot(acc, fam, i, j, gamma, lam, st, ws, c2, d)) return ws;
+    double nd[75];
+    for (int n = 0; n < 25; ++n) {
+        const Prim<double> w = fc_lattice(acc, d, i, j, n);
+        nd[n] = w.p - ws.p;
+        nd[25 + n] = w.u - ws.u;
+        nd[50 + n] = w.v - ws.v;
+    }
+    FcPoly P[4];
+    for (int q = 0; q < 4; ++q) fc_cell_poly(d, nd, q, P[q]);
+    double cut[kFcCuts + 1];
+    for (int q = 0; q < kFcCuts; ++q) {
+        const double c = fc_cut(d, q);
+        int k = q;
+        for (; k > 0 && cut[k - 1] > c; --k) cut[k] = cut[k - 1];
+        cut[k] = c;
+    }
+    cut[kFcCuts] = 2.0 * kFcPi;
+    FcSums S{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int q = 0; q < kFcCuts; ++q) {
+        if (cut[q + 1] - cut[q] < 1e-15) continue;
+        const FcPiece w = fc_piece(d, cut[q], cut[q + 1]);
+        for (int k = 0; k < 32; ++k)
+            fc_node(d, w, kGaussCos32[k], 0.5 * kFcPi * kGaussW32[k] * kGaussSin32[k],
+                    [&](int c) -> const FcPoly& { return P[c]; }, S);
+    }
+    return fc_value(ws, c2, S);
+}
+
+#if defined(__HIPCC__)
+// The same by one half-wavefront: lane = threadIdx.x & 31 of 32 lanes that agree on the
+// target; sh: LDS of this group.  The value is valid in every lane.
+struct FcShared { double nd[75]; FcPoly P[4]; };
+
+template <class A>
+__device__ __forceinline__ Prim<double> fc_point_group(const A& acc, int fam, int i, int j, double gamma, double lam,
+                                                       unsigned& st, FcShared& sh, int lane) {
+    Prim<double> ws;
+    double c2;
+    FcDisk d;
+    if (!fc_foot(acc, fam, i, j, gamma, lam, st, ws, c2, d)) return ws;
+    if (lane < 25) {
+        const Prim<double> w = fc_lattice(acc, d, i, j, lane);
+        sh.nd[lane] = w.p - ws.p;
+        sh.nd[25 + lane] = w.u - ws.u;
+        sh.nd[50 + lane] = w.v - ws.v;
+    }
+    __builtin_amdgcn_wave_barrier();
+    __threadfence_block();
+    if (lane < 4) fc_cell_poly(d, sh.nd, lane, sh.P[lane]);
+    __builtin_amdgcn_wave_barrier();
+    __threadfence_block();
+    // bitonic sort of the cuts across the group
+    double cut = lane < kFcCuts ? fc_cut(d, lane) : 2.0 * kFcPi;
+#pragma unroll
+    for (int k = 2; k <= 32; k *= 2)
+#pragma unroll
+        for (int m = k / 2; m > 0; m /= 2) {
+            const double o = __shfl_xor(cut, m, 32);
+            const bool up = (lane & k) == 0, low = (lane & m) == 0;
+            cut = up == low ? fmin(cut, o) : fmax(cut, o);
+        }
+    const double xc = kGaussCos32[lane], wt = 0.5 * kFcPi * kGaussW32[lane] * kGaussSin32[lane];
+    // lane q prepares piece q (cut[25 ..] = 2 pi: empty pieces)
+    const double next = __shfl_down(cut, 1, 32);
+    const FcPiece mine = fc_piece(d, cut, lane < 31 ? next : 2.0 * kFcPi);
+    FcSums S{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int q = 0; q < kFcCuts; ++q) {
+        const FcPiece w{__shfl(mine.dt, q, 32), __shfl(mine.cm, q, 32), __shfl(mine.sm, q, 32), __shfl(mine.code, q, 32)};
+        if (w.dt < 1e-15) continue;
+        fc_node(d, w, xc, wt, [&](int c) -> const FcPoly& { return sh.P[c]; }, S);
+    }
+#pragma unroll
+    for (int m = 16; m > 0; m /= 2) {
+        S.m += __shfl_xor(S.m, m, 32);
+        S.g += __shfl_xor(S.g, m, 32);
+        S.x += __shfl_xor(S.x, m, 32);
+        S.y += __shfl_xor(S.y, m, 32);
+        S.hx += __shfl_xor(S.hx, m, 32);
+        S.hy += __shfl_xor(S.hy, m, 32);
+    }
+    return fc_value(ws, c2, S);
+}
+#endif
 
 }  // namespace af

@@ -13,14 +13,6 @@
 
 namespace af {
 
-// Nine nodes of cell (ci, cj) in [x-node][y-node] order (Sec. 2; Sec. 4 R_Delta).
-template <class T, class A>
-AF_HD void cell_nodes(const A& acc, int ci, int cj, Prim<T> n[3][3]) {
-    n[0][0] = acc.node(F_V, ci, cj);      n[1][0] = acc.node(F_EH, ci, cj);     n[2][0] = acc.node(F_V, ci + 1, cj);
-    n[0][1] = acc.node(F_EV, ci, cj);     n[1][1] = acc.node(F_C, ci, cj);      n[2][1] = acc.node(F_EV, ci + 1, cj);
-    n[0][2] = acc.node(F_V, ci, cj + 1);  n[1][2] = acc.node(F_EH, ci, cj + 1); n[2][2] = acc.node(F_V, ci + 1, cj + 1);
-}
-
 // Node freezing (Sec. 6.1 step 1): c_K, Z_K and 1 / Z_K.  Sets SB_CFL if c_K dt / h > 1/2
 // (lam1 = dt / h) and SB_NONPHYS if the node state is not physical.
 template <class T>

@@ -1,6 +1,6 @@
 """Generate af_gauss.h: Gauss-Legendre nodes and weights on [0, 1] for the quadrature
-of the foot-centred exact update (32 points per angular piece, 10 per radial piece),
-with cos(pi x), sin(pi x) and sin(pi x / 2) of the nodes.
+of the foot-centred exact update (32 points per angular piece), with cos(pi x) and
+sin(pi x) of the nodes.
 
 Nodes are the roots of the Legendre polynomial P_n, found by Newton's method in
 40-digit arithmetic (mpmath) from the Chebyshev-like initial guesses
@@ -45,19 +45,14 @@ def main():
     lines = ["// Generated by gen_gauss.py -- do not edit.",
              "// Gauss-Legendre nodes and weights on [0, 1] (ascending nodes; weights sum to 1).",
              "#pragma once", "namespace af {"]
-    for n in (32, 10):
+    for n in (32,):
         xs, ws = rule(n)
         assert abs(sum(ws) - 1) < mp.mpf(10) ** -35
-        lines.append(f"constexpr double kGaussX{n}[{n}] = {{")
-        lines += [f"    {mp.nstr(x, 20, min_fixed=-1, max_fixed=1)}," for x in xs]
-        lines.append("};")
         lines.append(f"constexpr double kGaussW{n}[{n}] = {{")
         lines += [f"    {mp.nstr(w, 20, min_fixed=-1, max_fixed=1)}," for w in ws]
         lines.append("};")
-        # angle tables of the nodes: cos and sin of pi x (the clustering map of an angular
-        # piece) and sin of pi x / 2 (a radial piece spanning [0, pi/2])
-        for name, f in (("Cos", lambda x: mp.cos(mp.pi * x)), ("Sin", lambda x: mp.sin(mp.pi * x)),
-                        ("SinHalf", lambda x: mp.sin(mp.pi * x / 2))):
+        # cos and sin of pi x, the clustering map of an angular piece
+        for name, f in (("Cos", lambda x: mp.cos(mp.pi * x)), ("Sin", lambda x: mp.sin(mp.pi * x))):
             lines.append(f"constexpr double kGauss{name}{n}[{n}] = {{")
             lines += [f"    {mp.nstr(f(x), 20, min_fixed=-1, max_fixed=1)}," for x in xs]
             lines.append("};")
