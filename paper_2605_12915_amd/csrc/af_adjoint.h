@@ -12,7 +12,6 @@
 //      add is one accumulation.
 //   A  forward nodes by cell: A.node(fam, i, j) (fam = F_C: recovered centre).
 //   CT cotangent of the step's output: CT.get(plane, i, j) (periodic).
-//   LD cotangent of the increments: LD.get(tau * 12 + fam * 3 + q, i, j).
 // The floor() that locates a foot is piecewise constant: its derivative is zero.
 #pragma once
 #include "af_kernels.h"
@@ -434,19 +433,17 @@ AF_HD void node_adj(const T li[2][3], const T (&auv)[3][4], const T (&ap)[3][4],
 // Transposed increments of a pair of families at cell (i, j) (NX as in pair_blocks).  The
 // lines and blocks are those of the forward operator transposed, so every node of the
 // stencil gets one contribution per pair and variable: 128 scattered additions per cell
-// for the two pairs, against 251 with one per wedge.  A node whose six increment
-// cotangents are all zero contributes nothing.
-template <int NX, class T, class A_, class LD_, class O_>
-AF_HD void incr_adj(const A_& A, const LD_& LD, const O_& O, int i, int j, T gamma, T lam0, T lam1) {
+// for the two pairs, against 251 with one per wedge.  l1, l2: the cotangents of the two nodes'
+// increments [duration][u, v, p]; a node whose six are all zero contributes nothing.
+template <int NX, class T, class A_, class O_>
+AF_HD void incr_adj(const A_& A, const O_& O, int i, int j, const T (&l1)[2][3], const T (&l2)[2][3], T gamma, T lam0,
+                    T lam1) {
     constexpr int F1 = NX == 5 ? F_V : F_EH, F2 = NX == 5 ? F_EV : F_C;
-    T l1[2][3], l2[2][3];
     bool any1 = false, any2 = false;
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
-            l1[t][q] = LD.get(t * 12 + F1 * 3 + q, i, j);
-            l2[t][q] = LD.get(t * 12 + F2 * 3 + q, i, j);
             any1 = any1 || (l1[t][q] != T(0));
             any2 = any2 || (l2[t][q] != T(0));
         }

@@ -7,7 +7,7 @@
 // window entry instead of one per contribution):
 //   k_adj_fwd      forward intermediates recomputed from state_n (recovered centres
 //                  W^C, node increments of both durations); zeroes the accumulation
-//                  planes and starts the averages' cotangent at cot_np1's.
+//                  planes.
 //   k_adj_points   average update and space-time Simpson fluxes (transposed), then
 //                  for every target and duration the transposed point update (TAI:
 //                  density closure, Q2 evaluation of W and of the increments at the
@@ -17,9 +17,8 @@
 //   k_adj_incr     transposed node increments (Horner in r, freezing c_K, Z_K,
 //                  transposed monomial blocks and Lagrange-to-monomial transforms of
 //                  every wedge), then the transposed centre recovery (prim(U_c),
-//                  inverse Simpson, U(W) at the eight boundary nodes) applied to each
-//                  block's own share of lambda_C; scatters into the point and average
-//                  planes of cot_n.
+//                  inverse Simpson, U(W) at the eight boundary nodes); adds to the point
+//                  planes of cot_n and writes its average planes.
 // The floor() that locates a foot is piecewise constant: its derivative is zero
 // (the usual convention; the step is continuous across faces because R_h and I_h are).
 #include <hip/hip_runtime.h>
@@ -30,31 +29,6 @@
 #include "af_internal.h"
 
 namespace af {
-
-struct AdjNodes {
-    const double* s[16];
-    const double* C;
-    int nx, ny;
-    __device__ __forceinline__ size_t idx(int i, int j) const {
-        i = (i < 0) ? i + nx : (i >= nx ? i - nx : i);
-        j = (j < 0) ? j + ny : (j >= ny ? j - ny : j);
-        return (size_t)j * nx + i;
-    }
-    __device__ __forceinline__ double comp(int fam, int i, int j, int q) const {
-        const size_t k = idx(i, j);
-        if (fam == F_C) return C[(size_t)q * nx * ny + k];
-        return s[4 + 4 * fam + q][k];
-    }
-    __device__ __forceinline__ Prim<double> node(int fam, int i, int j) const {
-        const size_t k = idx(i, j);
-        if (fam == F_C) {
-            const size_t N = (size_t)nx * ny;
-            return {C[k], C[N + k], C[2 * N + k], C[3 * N + k]};
-        }
-        const int b = 4 + 4 * fam;
-        return {s[b][k], s[b + 1][k], s[b + 2][k], s[b + 3][k]};
-    }
-};
 
 // Scatter target of the reverse sweep: an LDS window of NPL planes over node-cells
 // [ri0, ri0 + RX) x [rj0, rj0 + RY) (unwrapped indices; the flush wraps them).
@@ -95,17 +69,6 @@ struct CotAcc {
         i = (i < 0) ? i + nx : (i >= nx ? i - nx : i);
         j = (j < 0) ? j + ny : (j >= ny ? j - ny : j);
         return s.p[k][(size_t)j * nx + i];
-    }
-};
-
-// One buffer of consecutive planes read by cell (the increments' cotangent).
-struct PlanesAcc {
-    const double* base;
-    int nx, ny;
-    __device__ __forceinline__ double get(int k, int i, int j) const {
-        i = (i < 0) ? i + nx : (i >= nx ? i - nx : i);
-        j = (j < 0) ? j + ny : (j >= ny ? j - ny : j);
-        return base[(size_t)k * nx * ny + (size_t)j * nx + i];
     }
 };
 
@@ -154,9 +117,8 @@ __device__ __forceinline__ int wrap_any(int v, int n) {
 // sweep: the tile's primitive node values (node-cells [-1, T+1)) and recovered centres
 // (cells [-1, T)) staged in LDS, then the increments of both durations at the tile's
 // own node-cells (every wedge of a node-cell in [0, T) lies in cells [-1, T)).  Writes
-// W^C of the tile's cells and the 24 increment planes, zeroes the tile's cells of the
-// planes the reverse sweep accumulates into, and starts the averages' cotangent at
-// cot_np1's (the averages enter the new averages with unit weight).
+// W^C of the tile's cells and the 24 increment planes, and zeroes the tile's cells of the
+// planes the point kernel accumulates into.
 template <int TX, int TY>
 struct IntTile {
     static constexpr int PX = TX + 2, PY = TY + 2, CX = TX + 1, CY = TY + 1;
@@ -188,10 +150,8 @@ constexpr int kFBX = 32, kFBY = 8, kFNT = kFBX * kFBY;
 using FwdTile = IntTile<kFBX, kFBY>;
 
 // two workgroups per CU (256 registers per lane)
-struct AvgPlanes { const double* src[4]; double* dst[4]; };
-
 __global__ void __launch_bounds__(kFNT, 2) k_adj_fwd(StatePtrs<double> prim, double* C, double* D, PlaneList Z,
-                                                     int nzero, AvgPlanes avg, int nx, int ny, int tiles_x, int ntiles,
+                                                     int nzero, int nx, int ny, int tiles_x, int ntiles,
                                                      double gamma, double lam0, double lam1, unsigned* status) {
     __shared__ FwdTile L;
     const int tile = xcd_tile(blockIdx.x, ntiles), tid = threadIdx.x;
@@ -224,8 +184,6 @@ __global__ void __launch_bounds__(kFNT, 2) k_adj_fwd(StatePtrs<double> prim, dou
     }
     if (own) {
         for (int q = 0; q < nzero; ++q) Z.p[q][g] = 0.0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) avg.dst[q][g] = avg.src[q][g];
     }
     __syncthreads();
     // recovered centres of cells [-1, T)
@@ -355,63 +313,120 @@ hipError_t prepare_points() {
                                (int)B::LDS);
 }
 
-// Transposed node increments and centre recovery for a BX x BY block of node-cells.
-// Every wedge of a node-cell in [0, B) lies in cells [-1, B) and its nodes in node-cells
-// [-1, B + 1): an LDS window over those node-cells collects the point-value, centre and
-// averages' contributions.  The centre recovery is linear in the centre cotangent, so
-// the block applies its transpose to the centre contributions of its own increments
-// (window cells [-1, B)) plus, for its own cells, the centre cotangent the point kernel
-// left in global memory; the neighbouring blocks do the same with theirs, and the sum
-// is the transpose applied to the total.  The centre nodes of those cells and their
-// boundary nodes stay inside the window.
-constexpr int kIBX = 32, kIBY = 8;
-using IncrWin = LdsWin<20, kIBX + 2, kIBY + 2>;   // planes 0..15 as the point window, 16..19 averages
+// Transposed node increments and centre recovery for a 16 x 8 block of node-cells, whose
+// share of cot_n the block completes by itself: it takes the pairs of families of the
+// node-cells [-1, B + 1), whose stencils reach node-cells [-2, B + 2) and are all that reach
+// [0, B), and the centre recovery of cells [-1, B).  The forward nodes of that window are
+// staged in LDS, the contributions accumulated in an LDS window of the same shape, and the
+// block's own node-cells added to global memory by plain loads and stores.  Rows hold all
+// planes side by side ([y][plane][x], an odd multiple of 16 doubles), so that two rows fall on
+// different banks.  The pairs are evaluated 1.41 times per node-cell for that; adding each
+// block's overlapping window to global memory by atomics instead took 30 k of the block's 52 k
+// cycles (512^2: 68 us against 61; 1000^2 272 and 236).
+constexpr int kIBX = 16, kIBY = 8, kINT = 256;
 
-__global__ void __launch_bounds__(kIBX * kIBY, 2) k_adj_incr(StatePtrs<double> prim, const double* C, const double* lD,
-                                                          const double* lC, PlaneList G, int nx, int ny,
-                                                          int tiles_x, int ntiles, double gamma, double lam0,
-                                                          double lam1) {
-    __shared__ double win[20 * (kIBX + 2) * (kIBY + 2)];
-    const int tile = xcd_tile(blockIdx.x, ntiles);
-    const int i0 = (tile % tiles_x) * kIBX, j0 = (tile / tiles_x) * kIBY;
-    const IncrWin O{win, i0 - 1, j0 - 1};
-    O.zero();
-    __syncthreads();
-    AdjNodes A{{}, C, nx, ny};
+struct IncrWin {
+    static constexpr int RX = kIBX + 4, RY = kIBY + 4, kPlane = RX + 1, kRX = 16 * kPlane, SIZE = RY * kRX;
+    double* a;
+    __device__ __forceinline__ int base(int x, int y) const { return (y + 2) * kRX + (x + 2); }
+    // planes 0..11 point values, 12..15 centres; the averages' (16..19) take the centres'
+    // place once those are consumed
+    __device__ __forceinline__ void addb(int pl, int b, int off, double v) const {
+        atomicAdd(a + b + ((pl >= 16 ? pl - 4 : pl) * kPlane + off), v);
+    }
+    __device__ __forceinline__ void node(int fam, int x, int y, const double g[4]) const {
+        const int b = base(x, y), pl = fam == F_C ? 12 : 4 * fam;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) A.s[k] = prim.p[k];
-    {
-        const int i = i0 + (int)threadIdx.x % kIBX;
-        const int j = j0 + (int)threadIdx.x / kIBX;
-        if (i < nx && j < ny) {
-            const PlanesAcc LD{lD, nx, ny};
-            incr_adj<5>(A, LD, O, i, j, gamma, lam0, lam1);
-            incr_adj<3>(A, LD, O, i, j, gamma, lam0, lam1);
+        for (int q = 0; q < 4; ++q) addb(pl + q, b, 0, g[q]);
+    }
+};
+
+struct IncrNodes {
+    const double* a;
+    __device__ __forceinline__ Prim<double> node(int fam, int x, int y) const {
+        const double* c = a + (y + 2) * IncrWin::kRX + (x + 2) + (fam == F_C ? 12 : 4 * fam) * IncrWin::kPlane;
+        return {c[0], c[IncrWin::kPlane], c[2 * IncrWin::kPlane], c[3 * IncrWin::kPlane]};
+    }
+};
+
+// dst: cot_n (0..11 point values, to which the point kernel has added; 12..15 averages); avg:
+// the averages' cotangent of cot_np1 (the averages enter the new averages with unit weight)
+constexpr size_t kIncrLds = 2 * IncrWin::SIZE * sizeof(double);
+
+struct IncrOut { double* dst[16]; const double* avg[4]; };
+
+__global__ void __launch_bounds__(kINT, 2) k_adj_incr(StatePtrs<double> prim, const double* C, const double* lD,
+                                                      const double* lC, IncrOut G, int nx, int ny, int tiles_x,
+                                                      int ntiles, double gamma, double lam0, double lam1) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    double* stage = reinterpret_cast<double*>(smem);
+    double* win = stage + IncrWin::SIZE;
+    const int tile = xcd_tile(blockIdx.x, ntiles), tid = threadIdx.x;
+    const int i0 = (tile % tiles_x) * kIBX, j0 = (tile / tiles_x) * kIBY;
+    const size_t N = (size_t)nx * ny;
+    const IncrWin O{win};
+    const IncrNodes A{stage};
+    // items of one round each: staged node-cells [-2, B + 2), pairs [-1, B + 1), centres [-1, B)
+    constexpr int PW = kIBX + 2, PH = kIBY + 2, CW = kIBX + 1, CH = kIBY + 1;
+    static_assert(IncrWin::RX * IncrWin::RY <= kINT && PW * PH <= kINT && CW * CH <= kINT, "one round each");
+    const int px = tid % PW - 1, py = tid / PW - 1, cx = tid % CW - 1, cy = tid / CW - 1;
+    const bool pair = tid < PW * PH, centre = tid < CW * CH;
+    double l[4][2][3], lW[4];
+    if (tid < IncrWin::RX * IncrWin::RY) {
+        const int wx = tid % IncrWin::RX, wy = tid / IncrWin::RX;
+        const size_t k = (size_t)wrap_any(j0 - 2 + wy, ny) * nx + wrap_any(i0 - 2 + wx, nx);
+        double v[16];
+#pragma unroll
+        for (int pl = 0; pl < 12; ++pl) v[pl] = prim.p[4 + pl][k];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[12 + q] = C[q * N + k];
+        if (pair) {
+            const double* d = lD + (size_t)wrap_any(j0 + py, ny) * nx + wrap_any(i0 + px, nx);
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int f = 0; f < 4; ++f)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) l[f][t][q] = d[(size_t)(t * 12 + f * 3 + q) * N];
         }
+        if (centre) {
+            const double* d = lC + (size_t)wrap_any(j0 + cy, ny) * nx + wrap_any(i0 + cx, nx);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) lW[q] = d[q * N];
+        }
+#pragma unroll
+        for (int pl = 0; pl < 16; ++pl) stage[wy * IncrWin::kRX + pl * IncrWin::kPlane + wx] = v[pl];
+    }
+    for (int e = tid; e < IncrWin::SIZE; e += kINT) win[e] = 0.0;
+    __syncthreads();
+    if (pair) {
+        incr_adj<5>(A, O, px, py, l[F_V], l[F_EV], gamma, lam0, lam1);
+        incr_adj<3>(A, O, px, py, l[F_EH], l[F_C], gamma, lam0, lam1);
     }
     __syncthreads();
-    // cells [-1, B): each centre entry is read (and cleared, so that the flush skips it)
-    // by one thread, which scatters into other planes only
-    const size_t N = (size_t)nx * ny;
-    constexpr int CW = kIBX + 1, CH = kIBY + 1;
-    for (int e = threadIdx.x; e < CW * CH; e += blockDim.x) {
-        const int i = i0 - 1 + e % CW, j = j0 - 1 + e / CW;
-        // past a ragged grid edge the window holds no contributions (the block's
-        // node-cells there are skipped), and the cell would index outside the grid
-        if (i >= nx || j >= ny) continue;
-        const bool own = i >= i0 && j >= j0 && i < nx && j < ny;
-        const int wb = O.base(i, j);
-        double lW[4];
+    // each centre entry is read (and cleared: the averages' contributions take its place) by
+    // one thread, which scatters into the point planes besides
+    if (centre) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            double* c = O.a + wb + (12 + k) * IncrWin::kPlane;
-            lW[k] = *c + (own ? lC[k * N + (size_t)j * nx + i] : 0.0);
+            double* c = win + O.base(cx, cy) + (12 + k) * IncrWin::kPlane;
+            lW[k] += *c;
             *c = 0.0;
         }
-        centre_adj(A, O, i, j, lW, gamma);
+        centre_adj(A, O, cx, cy, lW, gamma);
     }
     __syncthreads();
-    flush_window(O, G, nx, ny);
+    // the block's own node-cells, half the planes to a thread: planes 8 h .. 8 h + 7
+    const int x = tid % kIBX, y = tid / kIBX % kIBY, h = tid / (kIBX * kIBY);   // h: wave-uniform
+    if (i0 + x < nx && j0 + y < ny) {
+        const size_t g = (size_t)(j0 + y) * nx + (i0 + x);
+        const double* w = win + O.base(x, y);
+        double v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = h == 0 ? G.dst[q][g] : (q < 4 ? G.dst[8 + q][g] : G.avg[q - 4][g]);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) (h == 0 ? G.dst[q] : G.dst[8 + q])[g] = v[q] + w[(8 * h + q) * IncrWin::kPlane];
+    }
 }
 
 hipError_t launch_adjoint_f64(const StepArgs& a, const void* const cot1_[16], void* const cot0_[16]) {
@@ -432,14 +447,13 @@ hipError_t launch_adjoint_f64(const StepArgs& a, const void* const cot1_[16], vo
     for (int k = 0; k < 4; ++k) L.p[np++] = lC + k * N;
     for (int k = 0; k < 24; ++k) L.p[np++] = lD + k * N;
     // L lists the window planes in LdsWin order: point values, centres, increments
-    PlaneList Li = L;   // k_adj_incr's window: point values, centres (consumed in the block), averages
-    for (int k = 0; k < 4; ++k) Li.p[16 + k] = cot0.p[k];
-    AvgPlanes avg;
-    for (int k = 0; k < 4; ++k) { avg.src[k] = cot1.p[k]; avg.dst[k] = cot0.p[k]; }
+    IncrOut out;
+    for (int k = 0; k < 12; ++k) out.dst[k] = cot0.p[4 + k];
+    for (int k = 0; k < 4; ++k) { out.dst[12 + k] = cot0.p[k]; out.avg[k] = cot1.p[k]; }
     const double lam1 = a.dt / a.h, lam0 = 0.5 * lam1;
     {
         const int tx = (a.nx + kFBX - 1) / kFBX, nt = tx * ((a.ny + kFBY - 1) / kFBY);
-        hipLaunchKernelGGL(k_adj_fwd, dim3(nt), dim3(kFNT), 0, a.stream, prim, C, Dfwd, L, np, avg, a.nx, a.ny, tx, nt,
+        hipLaunchKernelGGL(k_adj_fwd, dim3(nt), dim3(kFNT), 0, a.stream, prim, C, Dfwd, L, np, a.nx, a.ny, tx, nt,
                            a.gamma, lam0, lam1, a.status);
     }
     if (a.ev_begin) (void)hipEventRecord(a.ev_begin, a.stream);
@@ -449,14 +463,18 @@ hipError_t launch_adjoint_f64(const StepArgs& a, const void* const cot1_[16], vo
     else launch_points<1, 8, 8, 2>(a, prim, C, Dfwd, cot1, L, lam0, lam1);
     {
         const int tx = (a.nx + kIBX - 1) / kIBX, nt = tx * ((a.ny + kIBY - 1) / kIBY);
-        hipLaunchKernelGGL(k_adj_incr, dim3(nt), dim3(kIBX * kIBY), 0, a.stream, prim, C, lD, lC, Li, a.nx, a.ny, tx, nt,
+        hipLaunchKernelGGL(k_adj_incr, dim3(nt), dim3(kINT), kIncrLds, a.stream, prim, C, lD, lC, out, a.nx, a.ny, tx, nt,
                            a.gamma, lam0, lam1);
     }
     if (a.ev_end) (void)hipEventRecord(a.ev_end, a.stream);
     return hipGetLastError();
 }
 
-hipError_t prepare_adjoint_f64() { return prepare_points<8, 8, 2>(); }
+hipError_t prepare_adjoint_f64() {
+    const hipError_t e = hipFuncSetAttribute((const void*)k_adj_incr, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             (int)kIncrLds);
+    return e != hipSuccess ? e : prepare_points<8, 8, 2>();
+}
 
 size_t scratch_bytes_adjoint_f64(int nx, int ny) { return (size_t)nx * ny * (4 + 24 + 4 + 24) * sizeof(double); }
 
