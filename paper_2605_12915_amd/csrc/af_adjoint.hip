@@ -30,33 +30,19 @@
 
 namespace af {
 
-// Scatter target of the reverse sweep: an LDS window of NPL planes over node-cells
-// [ri0, ri0 + RX) x [rj0, rj0 + RY) (unwrapped indices; the flush wraps them).
-// Planes: 0..11 point values (family * 4 + (rho, u, v, p)), 12..15 recovered
+// Scatter target of the point kernel: an LDS window of 40 planes over node-cells
+// [ri0, ri0 + R) x [rj0, rj0 + R) (unwrapped indices; the flush wraps them), the planes of a
+// row side by side.  Planes: 0..11 point values (family * 4 + (rho, u, v, p)), 12..15 recovered
 // centres, 16..39 increments (tau * 12 + family * 3 + (u, v, p)).
-template <int NPL, int RX, int RY>
-struct LdsWin {
+template <int R>
+struct PointWin {
+    static constexpr int kPlane = R, kRX = 40 * R, SIZE = R * kRX;
     double* a;
     int ri0, rj0;
-    static constexpr int kRX = RX, kPlane = RX * RY;
-    __device__ __forceinline__ void add(int pl, int i, int j, double v) const {
-        atomicAdd(a + (pl * RY + (j - rj0)) * RX + (i - ri0), v);
-    }
-    // offset of node-cell (i, j) within a plane; addb adds to plane pl at that offset
-    // plus a small constant one (so that every add of one cell's nodes shares a base)
-    __device__ __forceinline__ int base(int i, int j) const { return (j - rj0) * RX + (i - ri0); }
-    __device__ __forceinline__ void addb(int pl, int b, int off, double v) const {
-        atomicAdd(a + b + (pl * kPlane + off), v);
-    }
-    // add g = (d rho, d u, d v, d p) to node fam of cell (i, j)
-    __device__ __forceinline__ void node(int fam, int i, int j, const double g[4]) const {
-        const int b = fam == F_C ? 12 : 4 * fam, o = base(i, j);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) addb(b + q, o, 0, g[q]);
-    }
-    __device__ __forceinline__ void zero() const {
-        for (int e = threadIdx.x; e < NPL * RX * RY; e += blockDim.x) a[e] = 0.0;
-    }
+    // offset of node-cell (i, j); addb adds to plane pl at that offset plus a small constant
+    // one (so that every add of one cell's nodes shares a base)
+    __device__ __forceinline__ int base(int i, int j) const { return (j - rj0) * kRX + (i - ri0); }
+    __device__ __forceinline__ void addb(int pl, int b, int off, double v) const { atomicAdd(a + b + (pl * kPlane + off), v); }
 };
 
 struct PlaneList { double* p[40]; };
@@ -72,35 +58,30 @@ struct CotAcc {
     }
 };
 
-// The forward state of a block, staged in LDS over the node-cells of its scatter
-// window with the window's plane numbering: point values (0..11), recovered centres
-// (12..15), increments of both durations (16..39).
-template <int RX, int RY>
+// The forward state of a block, staged in LDS like its scatter window.
+template <int R>
 struct StageWin {
+    static constexpr int kPlane = R, kRX = 40 * R;
     const double* a;
     int ri0, rj0;
-    static constexpr int kRX = RX, kPlane = RX * RY;
-    __device__ __forceinline__ int base(int i, int j) const { return (j - rj0) * RX + (i - ri0); }
+    __device__ __forceinline__ int base(int i, int j) const { return (j - rj0) * kRX + (i - ri0); }
     __device__ __forceinline__ double at(int pl, int b, int off) const { return a[b + (pl * kPlane + off)]; }
-    __device__ __forceinline__ Prim<double> node(int fam, int b) const {
-        const int pl = fam == F_C ? 12 : 4 * fam;
-        return {at(pl, b, 0), at(pl + 1, b, 0), at(pl + 2, b, 0), at(pl + 3, b, 0)};
-    }
 };
 
-// Add an LDS window to its global planes (periodic wrap), one atomic per nonzero entry:
-// each thread takes whole node-cells of the window, wraps its global index once and
-// walks the planes (so the plane pointer is the same across the wavefront).
-template <int NPL, int RX, int RY>
-__device__ __forceinline__ void flush_window(const LdsWin<NPL, RX, RY>& w, const PlaneList& G, int nx, int ny) {
-    for (int e = threadIdx.x; e < RX * RY; e += blockDim.x) {
-        int i = w.ri0 + e % RX, j = w.rj0 + e / RX;
+// Add a window to its global planes (periodic wrap), one atomic per nonzero entry: each
+// thread takes whole node-cells of the window, wraps its global index once and walks the
+// planes (so the plane pointer is the same across the wavefront).
+template <int R>
+__device__ __forceinline__ void flush_window(const PointWin<R>& w, const PlaneList& G, int nx, int ny) {
+    for (int e = threadIdx.x; e < R * R; e += blockDim.x) {
+        int i = w.ri0 + e % R, j = w.rj0 + e / R;
         i = (i % nx + nx) % nx;
         j = (j % ny + ny) % ny;
         const size_t k = (size_t)j * nx + i;
+        const double* c = w.a + (e / R) * PointWin<R>::kRX + e % R;
 #pragma unroll 8
-        for (int pl = 0; pl < NPL; ++pl) {
-            const double v = w.a[pl * (RX * RY) + e];
+        for (int pl = 0; pl < 40; ++pl) {
+            const double v = c[pl * R];
             if (v != 0.0) atomicAdd(G.p[pl] + k, v);
         }
     }
@@ -229,16 +210,14 @@ __global__ void __launch_bounds__(kFNT, 2) k_adj_fwd(StatePtrs<double> prim, dou
 // 8x8 blocks: the staged state and the window take 79 KB, so two blocks share a CU and
 // one's staging overlaps the other's work (2% faster than 16x8 at one block per CU,
 // despite the larger window overlap, 1.89x against 1.63x).
-// The accumulation window's rows are padded to WX = 12 doubles (its twelfth column is
-// never written): with the block's rows split between the half-wavefronts as
-// {0, 2, 4, 6} and {1, 3, 5, 7}, the four rows a half-wavefront adds to at a common
-// offset start 0, 24, 48 and 72 doubles apart, i.e. in four distinct quarters of the
-// 64 LDS banks (with 11-double rows, rows 0 and 3 of four consecutive ones collide).
+// The planes of a window row lie side by side: 40 x 11 doubles from row to row, 24 modulo the
+// 32 that the banks hold, so that the four rows of 8 lanes that a half-wavefront reads or
+// adds to at a common offset start in four distinct quarters of the banks.
 template <int BX, int BY>
 struct PointBlock {
-    static constexpr int NT = 3 * BX * BY, RX = BX + 3, RY = BY + 3, WIN = RX * RY;
-    static constexpr int WX = BX == 8 ? 12 : RX, WWIN = WX * RY;
-    static constexpr size_t LDS = sizeof(double) * 40 * (WIN + WWIN);   // staged state + accumulators
+    static_assert(BX == BY, "square blocks");
+    static constexpr int NT = 3 * BX * BY, R = BX + 3, WIN = R * R;
+    static constexpr size_t LDS = sizeof(double) * 2 * 40 * WIN;   // staged state + accumulators
     static_assert(WIN <= NT, "one staging round");
     static_assert((BX * BY) % 64 == 0, "each wavefront holds one target family");
 };
@@ -252,14 +231,14 @@ __global__ void __launch_bounds__(3 * BX * BY, MINB)
                  int nx, int ny, int tiles_x, int ntiles, double gamma, double lam0, double lam1) {
     using B = PointBlock<BX, BY>;
     extern __shared__ __align__(16) unsigned char smem[];
-    double* stage = reinterpret_cast<double*>(smem);   // [40][RY][RX]
+    double* stage = reinterpret_cast<double*>(smem);   // [R][40][R]
     const int tile = xcd_tile(blockIdx.x, ntiles);
     const int i0 = (tile % tiles_x) * BX, j0 = (tile / tiles_x) * BY;
-    const LdsWin<40, B::WX, B::RY> O{stage + 40 * B::WIN, i0 - 1, j0 - 1};
-    O.zero();
+    const PointWin<B::R> O{stage + 40 * B::WIN, i0 - 1, j0 - 1};
+    for (int e = threadIdx.x; e < 40 * B::WIN; e += B::NT) O.a[e] = 0.0;
     if (threadIdx.x < B::WIN) {
         const int e = threadIdx.x;
-        const int i = wrap_any(i0 - 1 + e % B::RX, nx), j = wrap_any(j0 - 1 + e / B::RX, ny);
+        const int i = wrap_any(i0 - 1 + e % B::R, nx), j = wrap_any(j0 - 1 + e / B::R, ny);
         const size_t N = (size_t)nx * ny, k = (size_t)j * nx + i;
         double v[40];
 #pragma unroll
@@ -269,14 +248,12 @@ __global__ void __launch_bounds__(3 * BX * BY, MINB)
 #pragma unroll
         for (int q = 0; q < 24; ++q) v[16 + q] = Dfwd[q * N + k];
 #pragma unroll
-        for (int pl = 0; pl < 40; ++pl) stage[pl * B::WIN + e] = v[pl];
+        for (int pl = 0; pl < 40; ++pl) stage[(e / B::R) * (40 * B::R) + pl * B::R + e % B::R] = v[pl];
     }
     __syncthreads();
-    const StageWin<B::RX, B::RY> S{stage, i0 - 1, j0 - 1};
+    const StageWin<B::R> S{stage, i0 - 1, j0 - 1};
     const int cell = (int)threadIdx.x % (BX * BY), fam = (int)threadIdx.x / (BX * BY);   // wave-uniform
-    // rows of a half-wavefront: even rows in the first, odd rows in the second (8x8)
-    const int row = BX == 8 && BY == 8 ? 2 * ((cell / 8) % 4) + cell / 32 : cell / BX;
-    const int i = i0 + cell % BX, j = j0 + row;
+    const int i = i0 + cell % BX, j = j0 + cell / BX;
     if (i < nx && j < ny) {
         const CotAcc C1{cot1, nx, ny};
         unsigned fix;
