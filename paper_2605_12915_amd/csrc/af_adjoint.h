@@ -62,90 +62,87 @@ AF_HD void flux_y_T(const Prim<T>& w, T gamma, const T nu[4], T g[4]) {
     g[3] += nu[2] + nu[3] * w.v * gamma * gm1i;
 }
 
-// Transposed point update of target FAM at (i, j) for the duration tau = lam h;
+// Transposed point update of target FAM at (i, j) for the duration tau_t = lam h;
 // WP = the target's time-n value.  SCHEME 0: transported update (the increments are
-// interpolated at the foot, the density closure uses c^2 at the foot); SCHEME 1:
-// additive update (the target's own increments, c^2 frozen at the target).
+// interpolated at the foot, the density closure uses c^2 at the foot); the increment planes
+// hold u + du, v + dv and dp, as in the step, and so do their cotangents: what the
+// velocities themselves get from the foot is the sum of those planes' cotangents over the
+// durations, which the increments' kernel adds.  SCHEME 1: additive update (the
+// target's own increments, c^2 frozen at the target).
 // The forward value w is recomputed here and its cotangent formed from the flux
 // cotangents: lw = ws * (dF/dW)^T nuF + ws * (dG/dW)^T nuG (+ extra: the cotangent
-// of the new point value itself, for the full step).  The contributions to the
-// target's own node (through the first foot position) are added to gself, those to
-// the nodes of the two foot cells go to the window, one base offset per cell.
-//
-// The two Picard stages normally lie in one foot cell; then each node's contribution
-// through the first stage's u1 = Q2(u) is added to its second-stage contribution
-// before a single scatter.  MODE 0 does that and returns true for a target whose
-// stages lie in different cells, whose first-stage contributions it leaves out; MODE 1
-// recomputes such a target and scatters only those (the caller runs it for the rare
-// wavefronts that need it, so the common path keeps one scatter per node and plane).
+// of the new point value itself, for the full step).  The contributions to the target's own
+// node (through the first foot position) are added to gself, those to the increments go to
+// the window; those to the nodes of the two foot cells are returned (FootAdj).  MODE 1
+// returns them only.
+template <class T>
+struct FootAdj {
+    T lx1[3], ly1[3], lx2[3], ly2[3];   // Lagrange weights of the two Picard stages' positions
+    T l[4], lu1, lv1;                   // adjoint of Q2(W) at the second, of Q2(u), Q2(v) at the first
+    int wb1, wb2;                       // window offsets of their cells
+};
+
 template <int FAM, int SCHEME, int MODE, class T, class S_, class O_>
-AF_HD bool point_update_adj(const S_& S, const O_& O, int t, int i, int j, const Prim<T>& WP, T gamma, T lam,
-                            const T nuF[4], const T nuG[4], T ws, const T* extra, T gself[4]) {
+AF_HD void point_update_adj(const S_& S, const O_& O, int t, int i, int j, const Prim<T>& WP, T gamma, T lam,
+                            const T nuF[4], const T nuG[4], T ws, const T* extra, T gself[4], FootAdj<T>& R) {
     const T ox = T(FamOffset<FAM>::ox), oy = T(FamOffset<FAM>::oy);
     constexpr int RX = O_::kRX, SRX = S_::kRX;   // row strides of the window and of the staged state
+    constexpr bool SUM = SCHEME == 0;
     unsigned st = 0;
     // ---- forward recomputation ----
-    int cx1, cy1, cx2, cy2;
-    T xi1, eta1, xi2, eta2;
-    locate(ox - lam * WP.u, ox, cx1, xi1, st);
-    locate(oy - lam * WP.v, oy, cy1, eta1, st);
-    T lx1[3], dlx1[3], ly1[3], dly1[3];
-    lagr(xi1, lx1, dlx1);
-    lagr(eta1, ly1, dly1);
+    int cx, cy;
+    T xi, eta, dlx[3], dly[3];
+    locate(ox - lam * WP.u, ox, cx, xi, st);
+    locate(oy - lam * WP.v, oy, cy, eta, st);
+    lagr(xi, R.lx1, dlx);
+    lagr(eta, R.ly1, dly);
     T u1 = T(0), v1 = T(0), du1x = T(0), du1y = T(0), dv1x = T(0), dv1y = T(0);
-    T w1[3][3];   // tensor weights of the first foot (reused by the reverse scatter)
-    const int wb1 = O.base(i + cx1, j + cy1), sb1 = S.base(i + cx1, j + cy1);
-    {
+    R.wb1 = O.base(i + cx, j + cy);
+    const int sb1 = S.base(i + cx, j + cy);
 #pragma unroll
-        for (int a = 0; a < 3; ++a)
+    for (int a = 0; a < 3; ++a)
 #pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                const int f = fam_of(a, b), soff = (b == 2 ? SRX : 0) + (a == 2 ? 1 : 0);
-                const T nu_ = S.at(win_plane(f) + 1, sb1, soff), nv_ = S.at(win_plane(f) + 2, sb1, soff);
-                const T w = lx1[a] * ly1[b], wx = dlx1[a] * ly1[b], wy = lx1[a] * dly1[b];
-                w1[a][b] = w;
-                u1 += w * nu_;
-                v1 += w * nv_;
-                du1x += wx * nu_;
-                du1y += wy * nu_;
-                dv1x += wx * nv_;
-                dv1y += wy * nv_;
-            }
-    }
-    locate(ox - lam * u1, ox, cx2, xi2, st);
-    locate(oy - lam * v1, oy, cy2, eta2, st);
-    T lx2[3], dlx2[3], ly2[3], dly2[3];
-    lagr(xi2, lx2, dlx2);
-    lagr(eta2, ly2, dly2);
-    const int ci = i + cx2, cj = j + cy2;
+        for (int b = 0; b < 3; ++b) {
+            const int f = fam_of(a, b), soff = (b == 2 ? SRX : 0) + (a == 2 ? 1 : 0);
+            const T nu_ = S.at(win_plane(f) + 1, sb1, soff), nv_ = S.at(win_plane(f) + 2, sb1, soff);
+            const T w = R.lx1[a] * R.ly1[b], wx = dlx[a] * R.ly1[b], wy = R.lx1[a] * dly[b];
+            u1 += w * nu_;
+            v1 += w * nv_;
+            du1x += wx * nu_;
+            du1y += wy * nu_;
+            dv1x += wx * nv_;
+            dv1y += wy * nv_;
+        }
+    locate(ox - lam * u1, ox, cx, xi, st);
+    locate(oy - lam * v1, oy, cy, eta, st);
+    lagr(xi, R.lx2, dlx);
+    lagr(eta, R.ly2, dly);
+    R.wb2 = O.base(i + cx, j + cy);
+    const int sb2 = S.base(i + cx, j + cy);
     T Wf[4] = {T(0), T(0), T(0), T(0)}, dWx[4] = {T(0), T(0), T(0), T(0)}, dWy[4] = {T(0), T(0), T(0), T(0)};
     T Df[3] = {T(0), T(0), T(0)}, dDx[3] = {T(0), T(0), T(0)}, dDy[3] = {T(0), T(0), T(0)};
-    T w2[3][3];   // tensor weights of the second foot (reused by the reverse scatter)
-    const int wb2 = O.base(ci, cj), sb2 = S.base(ci, cj);
-    {
 #pragma unroll
-        for (int a = 0; a < 3; ++a)
+    for (int a = 0; a < 3; ++a)
 #pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                const T w = lx2[a] * ly2[b], wx = dlx2[a] * ly2[b], wy = lx2[a] * dly2[b];
-                w2[a][b] = w;
-                const int f = fam_of(a, b), soff = (b == 2 ? SRX : 0) + (a == 2 ? 1 : 0);
+        for (int b = 0; b < 3; ++b) {
+            const T w = R.lx2[a] * R.ly2[b], wx = dlx[a] * R.ly2[b], wy = R.lx2[a] * dly[b];
+            const int f = fam_of(a, b), soff = (b == 2 ? SRX : 0) + (a == 2 ? 1 : 0);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const T v = S.at(win_plane(f) + q, sb2, soff);
-                    Wf[q] += w * v; dWx[q] += wx * v; dWy[q] += wy * v;
-                }
-                if constexpr (SCHEME == 0) {
+            for (int q = 0; q < 4; ++q) {
+                if (SUM && (q == 1 || q == 2)) continue;
+                const T v = S.at(win_plane(f) + q, sb2, soff);
+                Wf[q] += w * v; dWx[q] += wx * v; dWy[q] += wy * v;
+            }
+            if constexpr (SUM) {
 #pragma unroll
-                    for (int q = 0; q < 3; ++q) {
-                        const T v = S.at(16 + t * 12 + f * 3 + q, sb2, soff);
-                        Df[q] += w * v; dDx[q] += wx * v; dDy[q] += wy * v;
-                    }
+                for (int q = 0; q < 3; ++q) {
+                    const T v = S.at(16 + t * 12 + f * 3 + q, sb2, soff);
+                    Df[q] += w * v; dDx[q] += wx * v; dDy[q] += wy * v;
                 }
             }
-    }
+        }
     const int wbP = O.base(i, j);
-    if constexpr (SCHEME == 1) {
+    if constexpr (!SUM) {
         const int sbP = S.base(i, j);
 #pragma unroll
         for (int q = 0; q < 3; ++q) Df[q] = S.at(16 + t * 12 + FAM * 3 + q, sbP, 0);
@@ -153,11 +150,11 @@ AF_HD bool point_update_adj(const S_& S, const O_& O, int t, int i, int j, const
     // ---- reverse ----
     // compose: rho = rho_f + dp rho_K / (gamma p_K), u = u_f + du, v = v_f + dv, p = p_f + dp,
     // with K the foot (SCHEME 0) or the target (SCHEME 1)
-    const T rK = SCHEME == 0 ? Wf[0] : WP.r, pK = SCHEME == 0 ? Wf[3] : WP.p;
+    const T rK = SUM ? Wf[0] : WP.r, pK = SUM ? Wf[3] : WP.p;
     const T qinv = T(1) / (gamma * pK), rq = rK * qinv;
     T lw[4] = {T(0), T(0), T(0), T(0)};
     {
-        const Prim<T> w{Wf[0] + Df[2] * rq, Wf[1] + Df[0], Wf[2] + Df[1], Wf[3] + Df[2]};
+        const Prim<T> w{Wf[0] + Df[2] * rq, SUM ? Df[0] : Wf[1] + Df[0], SUM ? Df[1] : Wf[2] + Df[1], Wf[3] + Df[2]};
         T nu[4];
         if constexpr (FAM != F_EH) {
 #pragma unroll
@@ -173,80 +170,98 @@ AF_HD bool point_update_adj(const S_& S, const O_& O, int t, int i, int j, const
 #pragma unroll
             for (int k = 0; k < 4; ++k) lw[k] += extra[k];
     }
-    T lWf[4], lDf[3];
-    lDf[0] = lw[1];
-    lDf[1] = lw[2];
-    lDf[2] = lw[3] + lw[0] * rq;
-    lWf[1] = lw[1];
-    lWf[2] = lw[2];
+    const T lDf[3] = {lw[1], lw[2], lw[3] + lw[0] * rq};
     const T ldq = lw[0] * Df[2] * qinv;
-    if constexpr (SCHEME == 0) {
-        lWf[0] = lw[0] + ldq;
-        lWf[3] = lw[3] - ldq * gamma * rq;   // rho_K / p_K = gamma rq
+    R.l[1] = SUM ? T(0) : lw[1];
+    R.l[2] = SUM ? T(0) : lw[2];
+    if constexpr (SUM) {
+        R.l[0] = lw[0] + ldq;
+        R.l[3] = lw[3] - ldq * gamma * rq;   // rho_K / p_K = gamma rq
     } else {
-        lWf[0] = lw[0];
-        lWf[3] = lw[3];
+        R.l[0] = lw[0];
+        R.l[3] = lw[3];
         // the frozen rho_K / (gamma p_K) at the target, and its own increments
-        gself[0] += ldq;
-        gself[3] -= ldq * gamma * rq;
+        if constexpr (MODE == 0) {
+            gself[0] += ldq;
+            gself[3] -= ldq * gamma * rq;
 #pragma unroll
-        for (int q = 0; q < 3; ++q) O.addb(16 + t * 12 + FAM * 3 + q, wbP, 0, lDf[q]);
+            for (int q = 0; q < 3; ++q) O.addb(16 + t * 12 + FAM * 3 + q, wbP, 0, lDf[q]);
+        }
     }
     // foot position: xi2 = 2 (off - floor(off)) - 1, off = ox - lam u1
     T lxi2 = T(0), leta2 = T(0);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) { lxi2 += lWf[q] * dWx[q]; leta2 += lWf[q] * dWy[q]; }
-    if constexpr (SCHEME == 0)
+    for (int q = 0; q < 4; ++q) {
+        if (SUM && (q == 1 || q == 2)) continue;
+        lxi2 += R.l[q] * dWx[q];
+        leta2 += R.l[q] * dWy[q];
+    }
+    if constexpr (SUM) {
 #pragma unroll
         for (int q = 0; q < 3; ++q) { lxi2 += lDf[q] * dDx[q]; leta2 += lDf[q] * dDy[q]; }
-    const T lu1 = T(-2) * lam * lxi2, lv1 = T(-2) * lam * leta2;
-    // Q2 values at the foot -> nodes of the foot cell, and the first stage's
-    // u1 = Q2(u) at (xi1, eta1): lu1, lv1 -> u, v of the first foot cell's nodes.  When
-    // both stages lie in one cell (the usual case) each node's two contributions are
-    // added before one scatter.
-    const bool same = wb1 == wb2;
-    if constexpr (MODE == 1) {
+    }
+    R.lu1 = T(-2) * lam * lxi2;
+    R.lv1 = T(-2) * lam * leta2;
+    if constexpr (MODE == 1) return;
+    if constexpr (SUM) {
 #pragma unroll
         for (int a = 0; a < 3; ++a)
 #pragma unroll
             for (int b = 0; b < 3; ++b) {
-                const T v = w1[a][b];
+                const T w = R.lx2[a] * R.ly2[b];
                 const int f = fam_of(a, b), off = (b == 2 ? RX : 0) + (a == 2 ? 1 : 0);
-                O.addb(win_plane(f) + 1, wb1, off, v * lu1);
-                O.addb(win_plane(f) + 2, wb1, off, v * lv1);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) O.addb(16 + t * 12 + f * 3 + q, R.wb2, off, w * lDf[q]);
             }
-        return false;
     }
+    const T lxi1 = R.lu1 * du1x + R.lv1 * dv1x, leta1 = R.lu1 * du1y + R.lv1 * dv1y;
+    gself[1] += T(-2) * lam * lxi1;
+    gself[2] += T(-2) * lam * leta1;
+}
+
+// Contributions to the nodes of a foot cell at window offset wb: the second stage of SECOND and
+// the first stage of FIRST of N durations that share the cell, one addition per node and plane.
+template <bool SUM, int N, bool FIRST, bool SECOND, class T, class O_>
+AF_HD void foot_scatter(const O_& O, int wb, const FootAdj<T>* R) {
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
-            const T w = w2[a][b], v = w1[a][b];
-            const int f = fam_of(a, b), off = (b == 2 ? RX : 0) + (a == 2 ? 1 : 0);
-            O.addb(win_plane(f), wb2, off, w * lWf[0]);
-            O.addb(win_plane(f) + 1, wb2, off, w * lWf[1] + (same ? v * lu1 : T(0)));
-            O.addb(win_plane(f) + 2, wb2, off, w * lWf[2] + (same ? v * lv1 : T(0)));
-            O.addb(win_plane(f) + 3, wb2, off, w * lWf[3]);
-            if constexpr (SCHEME == 0)
+            T g[4] = {T(0), T(0), T(0), T(0)};
 #pragma unroll
-                for (int q = 0; q < 3; ++q) O.addb(16 + t * 12 + f * 3 + q, wb2, off, w * lDf[q]);
+            for (int t = 0; t < N; ++t) {
+                if constexpr (SECOND) {
+                    const T w = R[t].lx2[a] * R[t].ly2[b];
+                    g[0] += w * R[t].l[0];
+                    if constexpr (!SUM) { g[1] += w * R[t].l[1]; g[2] += w * R[t].l[2]; }
+                    g[3] += w * R[t].l[3];
+                }
+                if constexpr (FIRST) {
+                    const T w = R[t].lx1[a] * R[t].ly1[b];
+                    g[1] += w * R[t].lu1;
+                    g[2] += w * R[t].lv1;
+                }
+            }
+            const int pl = win_plane(fam_of(a, b)), off = (b == 2 ? O_::kRX : 0) + (a == 2 ? 1 : 0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if ((q == 1 || q == 2) ? (FIRST || (SECOND && !SUM)) : SECOND) O.addb(pl + q, wb, off, g[q]);
         }
-    const T lxi1 = lu1 * du1x + lv1 * dv1x, leta1 = lu1 * du1y + lv1 * dv1y;
-    gself[1] += T(-2) * lam * lxi1;
-    gself[2] += T(-2) * lam * leta1;
-    return !same;
 }
 
 // Reverse sweep of one target (family FAM of node-cell (i, j)): the adjoints of the
 // edge fluxes it feeds, from the averages' cotangents, then of its three time levels
 // (w^n directly, w^{n+1/2} and w^{n+1} through the transposed point update).
-// MODE 0 returns a bit per duration (1: tau = dt/2, 2: tau = dt) whose Picard stages
-// left one cell; MODE 1, given those bits, scatters the first-stage contributions that
-// MODE 0 left out (everything it needs is reloaded, so that the common path does not
-// keep it live).
+// The two Picard stages of both durations normally lie in one foot cell: each node then
+// gets one addition per plane for all four.  MODE 0 does that and returns 1 for a target
+// whose feet lie in different cells, whose contributions to the foot cells it leaves out;
+// MODE 1 recomputes such a target and scatters those, stage by stage (the caller runs it for
+// the rare wavefronts that need it, so that the common path keeps one scatter per node and
+// plane and nothing live for the other).
 template <int FAM, int SCHEME, int MODE, class T, class S_, class CT, class O_>
 AF_HD unsigned point_adj_target(const S_& S, const CT& cot1, const O_& O, int i, int j, T gamma, T lam0, T lam1,
                                 unsigned fix = 0) {
+    constexpr bool SUM = SCHEME == 0;
     // cotangents of the time-integrated edge fluxes at this node: F at V and Ev, G at
     // V and Eh; spatial Simpson weights 1/6 (V, two edges each) and 4/6 (edge midpoints)
     T nuF[4] = {T(0), T(0), T(0), T(0)}, nuG[4] = {T(0), T(0), T(0), T(0)};
@@ -271,18 +286,9 @@ AF_HD unsigned point_adj_target(const S_& S, const CT& cot1, const O_& O, int i,
     const int pl = win_plane(FAM);
     const Prim<T> w0{S.at(pl, sb, 0), S.at(pl + 1, sb, 0), S.at(pl + 2, sb, 0), S.at(pl + 3, sb, 0)};
     T g[4] = {T(0), T(0), T(0), T(0)};
-    if constexpr (MODE == 1) {
-        if (fix & 1u)
-            point_update_adj<FAM, SCHEME, 1>(S, O, 0, i, j, w0, gamma, lam0, nuF, nuG, T(4.0 / 6.0), (const T*)nullptr, g);
-        if (fix & 2u) {
-            const T extra[4] = {cot1.get(4 + 4 * FAM, i, j), cot1.get(5 + 4 * FAM, i, j), cot1.get(6 + 4 * FAM, i, j),
-                                cot1.get(7 + 4 * FAM, i, j)};
-            point_update_adj<FAM, SCHEME, 1>(S, O, 1, i, j, w0, gamma, lam1, nuF, nuG, T(1.0 / 6.0), extra, g);
-        }
-        return 0u;
-    }
+    if (MODE == 1 && !fix) return 0u;
     // time level n (time-Simpson weight 1/6): the node itself
-    {
+    if constexpr (MODE == 0) {
         T nu[4];
         if constexpr (FAM != F_EH) {
 #pragma unroll
@@ -296,17 +302,26 @@ AF_HD unsigned point_adj_target(const S_& S, const CT& cot1, const O_& O, int i,
         }
     }
     // n + 1/2 (weight 4/6) and n + 1 (weight 1/6; also an output of the step)
-    unsigned out = 0u;
-    if (point_update_adj<FAM, SCHEME, 0>(S, O, 0, i, j, w0, gamma, lam0, nuF, nuG, T(4.0 / 6.0), (const T*)nullptr,
-                                         g))
-        out |= 1u;
+    FootAdj<T> R[2];
+    point_update_adj<FAM, SCHEME, MODE>(S, O, 0, i, j, w0, gamma, lam0, nuF, nuG, T(4.0 / 6.0), (const T*)nullptr, g,
+                                        R[0]);
     const T extra[4] = {cot1.get(4 + 4 * FAM, i, j), cot1.get(5 + 4 * FAM, i, j), cot1.get(6 + 4 * FAM, i, j),
                         cot1.get(7 + 4 * FAM, i, j)};
-    if (point_update_adj<FAM, SCHEME, 0>(S, O, 1, i, j, w0, gamma, lam1, nuF, nuG, T(1.0 / 6.0), extra, g))
-        out |= 2u;
+    point_update_adj<FAM, SCHEME, MODE>(S, O, 1, i, j, w0, gamma, lam1, nuF, nuG, T(1.0 / 6.0), extra, g, R[1]);
+    if constexpr (MODE == 1) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) O.addb(pl + q, wb, 0, g[q]);
-    return out;
+        for (int t = 0; t < 2; ++t) {
+            foot_scatter<SUM, 1, false, true>(O, R[t].wb2, R + t);
+            foot_scatter<SUM, 1, true, false>(O, R[t].wb1, R + t);
+        }
+        return 0u;
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) O.addb(pl + q, wb, 0, g[q]);
+        const bool same = R[0].wb1 == R[0].wb2 && R[1].wb1 == R[0].wb2 && R[1].wb2 == R[0].wb2;
+        if (same) foot_scatter<SUM, 2, true, true>(O, R[0].wb2, R);
+        return same ? 0u : 1u;
+    }
 }
 
 // Transposed line transform (see line): coefficients' adjoint -> nodes' adjoint.
@@ -435,9 +450,11 @@ AF_HD void node_adj(const T li[2][3], const T (&auv)[3][4], const T (&ap)[3][4],
 // stencil gets one contribution per pair and variable: 128 scattered additions per cell
 // for the two pairs, against 251 with one per wedge.  l1, l2: the cotangents of the two nodes'
 // increments [duration][u, v, p]; a node whose six are all zero contributes nothing.
+// sum: the point kernel's increment planes held u + du and v + dv, so the nodes' velocities get
+// the cotangents of both durations besides (SCHEME 0).
 template <int NX, class T, class A_, class O_>
-AF_HD void incr_adj(const A_& A, const O_& O, int i, int j, const T (&l1)[2][3], const T (&l2)[2][3], T gamma, T lam0,
-                    T lam1) {
+AF_HD void incr_adj(const A_& A, const O_& O, int i, int j, const T (&l1)[2][3], const T (&l2)[2][3], bool sum, T gamma,
+                    T lam0, T lam1) {
     constexpr int F1 = NX == 5 ? F_V : F_EH, F2 = NX == 5 ? F_EV : F_C;
     bool any1 = false, any2 = false;
 #pragma unroll
@@ -484,9 +501,9 @@ AF_HD void incr_adj(const A_& A, const O_& O, int i, int j, const T (&l1)[2][3],
     scale_acc(la1, Z1);
     scale_acc(la2, Z2);
     stage_fence(la1, la2);
-    pair_scatter<NX, 1>(O, i, j, la1, la2, T(0), T(0));
+    pair_scatter<NX, 1>(O, i, j, la1, la2, sum ? l1[0][0] + l1[1][0] : T(0), sum ? l2[0][0] + l2[1][0] : T(0));
     stage_fence(la1, la2);
-    pair_scatter<NX, 2>(O, i, j, la1, la2, T(0), T(0));
+    pair_scatter<NX, 2>(O, i, j, la1, la2, sum ? l1[0][1] + l1[1][1] : T(0), sum ? l2[0][1] + l2[1][1] : T(0));
 }
 
 template <class T>

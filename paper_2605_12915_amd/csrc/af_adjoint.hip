@@ -87,8 +87,7 @@ __device__ __forceinline__ void flush_window(const PointWin<R>& w, const PlaneLi
     }
 }
 
-// Periodic index: one shift (offsets of at most one grid length) or a modulo.
-__device__ __forceinline__ int wrap1(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
+// Periodic index.
 __device__ __forceinline__ int wrap_any(int v, int n) {
     v %= n;
     return v < 0 ? v + n : v;
@@ -97,7 +96,8 @@ __device__ __forceinline__ int wrap_any(int v, int n) {
 // Forward intermediates of a TX x TY tile, recomputed from state_n for the reverse
 // sweep: the tile's primitive node values (node-cells [-1, T+1)) and recovered centres
 // (cells [-1, T)) staged in LDS, then the increments of both durations at the tile's
-// own node-cells (every wedge of a node-cell in [0, T) lies in cells [-1, T)).  Writes
+// own node-cells (every wedge of a node-cell in [0, T) lies in cells [-1, T); with `sum`
+// u + du and v + dv in place of du and dv, as the point kernel takes them).  Writes
 // W^C of the tile's cells and the 24 increment planes, and zeroes the tile's cells of the
 // planes the point kernel accumulates into.
 template <int TX, int TY>
@@ -132,7 +132,7 @@ using FwdTile = IntTile<kFBX, kFBY>;
 
 // two workgroups per CU (256 registers per lane)
 __global__ void __launch_bounds__(kFNT, 2) k_adj_fwd(StatePtrs<double> prim, double* C, double* D, PlaneList Z,
-                                                     int nzero, int nx, int ny, int tiles_x, int ntiles,
+                                                     int nzero, bool sum, int nx, int ny, int tiles_x, int ntiles,
                                                      double gamma, double lam0, double lam1, unsigned* status) {
     __shared__ FwdTile L;
     const int tile = xcd_tile(blockIdx.x, ntiles), tid = threadIdx.x;
@@ -196,7 +196,11 @@ __global__ void __launch_bounds__(kFNT, 2) k_adj_fwd(StatePtrs<double> prim, dou
     if (own) {
         const IntAcc<kFBX, kFBY> A{&L};
         const PolAbs<double> pol{gamma, 1.0 / (gamma - 1.0)};
-        cell_increments(A, ox, oy, pol, lam0, lam1, st, [&](int pl, double v) { D[(size_t)pl * N + g] = v; });
+        cell_increments(A, ox, oy, pol, lam0, lam1, st, [&](int pl, double v) {
+            const int fam = (pl % 12) / 3, q = pl % 3;
+            if (q < 2 && sum) v += q == 0 ? A.node(fam, ox, oy).u : A.node(fam, ox, oy).v;
+            D[(size_t)pl * N + g] = v;
+        });
     }
     if (st) atomicOr(status, st);
 }
@@ -213,6 +217,10 @@ __global__ void __launch_bounds__(kFNT, 2) k_adj_fwd(StatePtrs<double> prim, dou
 // The planes of a window row lie side by side: 40 x 11 doubles from row to row, 24 modulo the
 // 32 that the banks hold, so that the four rows of 8 lanes that a half-wavefront reads or
 // adds to at a common offset start in four distinct quarters of the banks.
+// Bound by the LDS additions and by two wavefronts per SIMD hiding little of the FP64 chains:
+// both durations' feet in one cell share an addition per node and plane, and the velocities'
+// part of the increment planes is left to the increments' kernel (SCHEME 0; 512^2: 104.7 -> 94.0
+// us, 1000^2 461 -> 438).
 template <int BX, int BY>
 struct PointBlock {
     static_assert(BX == BY, "square blocks");
@@ -260,7 +268,7 @@ __global__ void __launch_bounds__(3 * BX * BY, MINB)
         if (fam == F_V) fix = point_adj_target<F_V, SCHEME, 0>(S, C1, O, i, j, gamma, lam0, lam1);
         else if (fam == F_EV) fix = point_adj_target<F_EV, SCHEME, 0>(S, C1, O, i, j, gamma, lam0, lam1);
         else fix = point_adj_target<F_EH, SCHEME, 0>(S, C1, O, i, j, gamma, lam0, lam1);
-        // targets whose Picard stages left one cell (rare): their first-stage share
+        // targets whose feet lie in different cells (rare): their shares of those cells
         if (__any(fix != 0u)) {
             if (fam == F_V) point_adj_target<F_V, SCHEME, 1>(S, C1, O, i, j, gamma, lam0, lam1, fix);
             else if (fam == F_EV) point_adj_target<F_EV, SCHEME, 1>(S, C1, O, i, j, gamma, lam0, lam1, fix);
@@ -333,7 +341,7 @@ constexpr size_t kIncrLds = 2 * IncrWin::SIZE * sizeof(double);
 struct IncrOut { double* dst[16]; const double* avg[4]; };
 
 __global__ void __launch_bounds__(kINT, 2) k_adj_incr(StatePtrs<double> prim, const double* C, const double* lD,
-                                                      const double* lC, IncrOut G, int nx, int ny, int tiles_x,
+                                                      const double* lC, IncrOut G, bool sum, int nx, int ny, int tiles_x,
                                                       int ntiles, double gamma, double lam0, double lam1) {
     extern __shared__ __align__(16) unsigned char smem[];
     double* stage = reinterpret_cast<double*>(smem);
@@ -377,8 +385,8 @@ __global__ void __launch_bounds__(kINT, 2) k_adj_incr(StatePtrs<double> prim, co
     for (int e = tid; e < IncrWin::SIZE; e += kINT) win[e] = 0.0;
     __syncthreads();
     if (pair) {
-        incr_adj<5>(A, O, px, py, l[F_V], l[F_EV], gamma, lam0, lam1);
-        incr_adj<3>(A, O, px, py, l[F_EH], l[F_C], gamma, lam0, lam1);
+        incr_adj<5>(A, O, px, py, l[F_V], l[F_EV], sum, gamma, lam0, lam1);
+        incr_adj<3>(A, O, px, py, l[F_EH], l[F_C], sum, gamma, lam0, lam1);
     }
     __syncthreads();
     // each centre entry is read (and cleared: the averages' contributions take its place) by
@@ -423,15 +431,15 @@ hipError_t launch_adjoint_f64(const StepArgs& a, const void* const cot1_[16], vo
     for (int k = 4; k < 16; ++k) L.p[np++] = cot0.p[k];
     for (int k = 0; k < 4; ++k) L.p[np++] = lC + k * N;
     for (int k = 0; k < 24; ++k) L.p[np++] = lD + k * N;
-    // L lists the window planes in LdsWin order: point values, centres, increments
+    // L lists the window planes in PointWin order: point values, centres, increments
     IncrOut out;
     for (int k = 0; k < 12; ++k) out.dst[k] = cot0.p[4 + k];
     for (int k = 0; k < 4; ++k) { out.dst[12 + k] = cot0.p[k]; out.avg[k] = cot1.p[k]; }
     const double lam1 = a.dt / a.h, lam0 = 0.5 * lam1;
     {
         const int tx = (a.nx + kFBX - 1) / kFBX, nt = tx * ((a.ny + kFBY - 1) / kFBY);
-        hipLaunchKernelGGL(k_adj_fwd, dim3(nt), dim3(kFNT), 0, a.stream, prim, C, Dfwd, L, np, a.nx, a.ny, tx, nt,
-                           a.gamma, lam0, lam1, a.status);
+        hipLaunchKernelGGL(k_adj_fwd, dim3(nt), dim3(kFNT), 0, a.stream, prim, C, Dfwd, L, np, a.scheme == 0,
+                           a.nx, a.ny, tx, nt, a.gamma, lam0, lam1, a.status);
     }
     if (a.ev_begin) (void)hipEventRecord(a.ev_begin, a.stream);
     // point kernel: 8x8-cell blocks, two per CU (16x8 blocks at one per CU, whose
@@ -440,8 +448,8 @@ hipError_t launch_adjoint_f64(const StepArgs& a, const void* const cot1_[16], vo
     else launch_points<1, 8, 8, 2>(a, prim, C, Dfwd, cot1, L, lam0, lam1);
     {
         const int tx = (a.nx + kIBX - 1) / kIBX, nt = tx * ((a.ny + kIBY - 1) / kIBY);
-        hipLaunchKernelGGL(k_adj_incr, dim3(nt), dim3(kINT), kIncrLds, a.stream, prim, C, lD, lC, out, a.nx, a.ny, tx, nt,
-                           a.gamma, lam0, lam1);
+        hipLaunchKernelGGL(k_adj_incr, dim3(nt), dim3(kINT), kIncrLds, a.stream, prim, C, lD, lC, out, a.scheme == 0,
+                           a.nx, a.ny, tx, nt, a.gamma, lam0, lam1);
     }
     if (a.ev_end) (void)hipEventRecord(a.ev_end, a.stream);
     return hipGetLastError();

@@ -201,8 +201,8 @@ int main() {
     for (int f = 0; f < 4; ++f)
         for (int t = 0; t < 2; ++t)
             for (int q = 0; q < 3; ++q) l[f][t][q] = lD.get(t * 12 + f * 3 + q, 2, 2);
-    incr_adj<5>(A, O, 2, 2, l[F_V], l[F_EV], gamma, lam0, lam1);
-    incr_adj<3>(A, O, 2, 2, l[F_EH], l[F_C], gamma, lam0, lam1);
+    incr_adj<5>(A, O, 2, 2, l[F_V], l[F_EV], true, gamma, lam0, lam1);
+    incr_adj<3>(A, O, 2, 2, l[F_EH], l[F_C], true, gamma, lam0, lam1);
     const long adj_incr = total() - a1;
     a1 = total();
     const Cnt lW[4] = {1e-2, 1e-2, 1e-2, 1e-2};

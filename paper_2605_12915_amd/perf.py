@@ -29,7 +29,7 @@ import os
 
 ALGO_FLOPS_PER_CELL_F64 = 3058
 ALGO_BYTES_PER_CELL_F64 = 256
-ALGO_FLOPS_PER_CELL_ADJ = 10583
+ALGO_FLOPS_PER_CELL_ADJ = 9937
 ALGO_BYTES_PER_CELL_ADJ = 384
 ALGO_BYTES_PER_CELL_F32 = 160      # 16 float planes each way + 4 compensation planes read and written
 HBM_PEAK_GBS = 8000.0
