@@ -48,8 +48,11 @@ _ADJ = ["csrc/af_adjoint.hip", "csrc/af_adjoint.h", "csrc/af_kernels.h", "csrc/a
 # the three kernels of one adjoint step (TAI point update)
 ADJOINT_KERNELS = ["af::k_adj_fwd", "af::k_adj_points<0, 8, 8, 2>", "af::k_adj_incr"]
 KERNEL_SOURCES = {
-    "af::k_fused<double, af::PolAbs<double>, 15, 10, 512, 0, false, 4, 16, true, true>": ["csrc/af_fused.hip"] + _STEP,
-    "af::k_fused<double, af::PolAbs<double>, 8, 8, 256, 0, false, 1, 0, true, true>": ["csrc/af_fused.hip"] + _STEP,
+    # the step kernels of both point updates (0: transported, 1: additive)
+    **{f"af::k_fused<double, af::PolAbs<double>, 15, 10, 512, {s}, false, 4, 16, true, true>":
+       ["csrc/af_fused.hip"] + _STEP for s in (0, 1)},
+    **{f"af::k_fused<double, af::PolAbs<double>, 8, 8, 256, {s}, false, 1, 0, true, true>":
+       ["csrc/af_fused.hip"] + _STEP for s in (0, 1)},
     "af::k_fused<float, af::PolPert<float>, 31, 10, 512, 0, true, 4, 32, true, false>": ["csrc/af_fused_f32.hip"] + _STEP,
     "af::k_fused<float, af::PolPert<float>, 8, 8, 256, 0, true, 4, 0, true, true>":
         ["csrc/af_fused_f32_small.hip", "csrc/af_fused_f32.hip"] + _STEP,
