@@ -971,6 +971,9 @@ const char* af_dominant_kernel(af_ctx* c) {
     if (c && c->f32 && small)
         return rb ? "af::k_fused<float, af::PolPert<float>, 8, 8, 256, 1, true, 4, 0, true, true>"
                   : "af::k_fused<float, af::PolPert<float>, 8, 8, 256, 0, true, 4, 0, true, true>";
+    if (c && c->f32 && af::one_tile_per_cu_f32(c->cfg.nx, c->cfg.ny))
+        return rb ? "af::k_fused<float, af::PolPert<float>, 31, 10, 1024, 1, true, 4, 32, true, false>"
+                  : "af::k_fused<float, af::PolPert<float>, 31, 10, 1024, 0, true, 4, 32, true, false>";
     if (c && c->f32)
         return rb ? "af::k_fused<float, af::PolPert<float>, 31, 10, 512, 1, true, 4, 32, true, false>"
                   : "af::k_fused<float, af::PolPert<float>, 31, 10, 512, 0, true, 4, 32, true, false>";

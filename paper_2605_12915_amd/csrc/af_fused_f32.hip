@@ -19,7 +19,15 @@ namespace af {
 // family 1.953 ms, both 1.905 ms; all four give identical bits.  Then the phase-2
 // family fence (no more scratch traffic from spills) 1.826 ms and the FP64 row layout
 // of the staged arrays (bank conflicts cut eightfold) 1.742 ms, identical bits.
+// (at 4096^2 now 1.46 ms: the folded increments, the interpolation of u + du and the
+// field-by-field order of the points; VALU issue bound at 61% of its rate.)
 constexpr int kFTX = 31, kFTY = 10, kFNT = 512, kFMinW = 4, kFRW = 32;
+
+// A grid of at most one such tile per CU (of 256) has no second workgroup to share a CU with:
+// 1024 threads then take the tile in half the rounds, with the same wavefronts per SIMD.  us
+// per step with 512 and 1024 threads: 192^2 11.9 and 11.4, 224^2 12.2 and 11.9, 256^2 12.6 and 12.2;
+// at 288^2 (290 tiles) 18.3 and 20.9.
+constexpr int kFNTWide = 1024;
 
 PolPert<float> pert_pol_f32(const double bg[4], double g) {
     const double r0 = bg[0], u0 = bg[1], v0 = bg[2], p0 = bg[3];
@@ -34,11 +42,16 @@ PolPert<float> pert_pol_f32(const double bg[4], double g) {
 
 hipError_t launch_step_fused_f32(const StepArgs& a) {
     if (small_grid(true, a.nx, a.ny)) return launch_step_fused_f32_small(a);
-    return launch_fused<float, PolPert<float>, kFTX, kFTY, kFNT, true, kFMinW, kFRW, true>(a, pert_pol_f32(a.bg, a.gamma));
+    const PolPert<float> pol = pert_pol_f32(a.bg, a.gamma);
+    if (one_tile_per_cu_f32(a.nx, a.ny))
+        return launch_fused<float, PolPert<float>, kFTX, kFTY, kFNTWide, true, kFMinW, kFRW, true>(a, pol);
+    return launch_fused<float, PolPert<float>, kFTX, kFTY, kFNT, true, kFMinW, kFRW, true>(a, pol);
 }
 
 hipError_t prepare_fused_f32(int nx, int ny) {
     if (small_grid(true, nx, ny)) return prepare_fused_f32_small();
+    if (one_tile_per_cu_f32(nx, ny))
+        return prepare_fused<float, PolPert<float>, kFTX, kFTY, kFNTWide, true, kFMinW, kFRW, true>();
     return prepare_fused<float, PolPert<float>, kFTX, kFTY, kFNT, true, kFMinW, kFRW, true>();
 }
 

@@ -62,6 +62,8 @@ inline bool small_grid(bool f32, int nx, int ny) {
     const long long tiles = ((nx + 7LL) / 8) * ((ny + 7LL) / 8);
     return tiles <= (f32 ? 640 : 256);
 }
+// FP32 grids of at most one 31x10 tile per CU.
+inline bool one_tile_per_cu_f32(int nx, int ny) { return ((nx + 30LL) / 31) * ((ny + 9LL) / 10) <= 256; }
 hipError_t prepare_fused_f64(int nx, int ny);
 hipError_t prepare_adjoint_f64();
 hipError_t launch_step_split_f64(const StepArgs& a);

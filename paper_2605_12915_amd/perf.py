@@ -53,7 +53,8 @@ KERNEL_SOURCES = {
        ["csrc/af_fused.hip"] + _STEP for s in (0, 1)},
     **{f"af::k_fused<double, af::PolAbs<double>, 8, 8, 256, {s}, false, 1, 0, true, true>":
        ["csrc/af_fused.hip"] + _STEP for s in (0, 1)},
-    "af::k_fused<float, af::PolPert<float>, 31, 10, 512, 0, true, 4, 32, true, false>": ["csrc/af_fused_f32.hip"] + _STEP,
+    **{f"af::k_fused<float, af::PolPert<float>, 31, 10, {nt}, 0, true, 4, 32, true, false>":
+       ["csrc/af_fused_f32.hip"] + _STEP for nt in (512, 1024)},
     "af::k_fused<float, af::PolPert<float>, 8, 8, 256, 0, true, 4, 0, true, true>":
         ["csrc/af_fused_f32_small.hip", "csrc/af_fused_f32.hip"] + _STEP,
     "af::k_fused_batch_direct<31, 10, 512, 4, 0, 32>": ["csrc/af_batch.hip", "csrc/af_batch.h"] + _STEP,

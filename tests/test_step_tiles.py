@@ -15,8 +15,9 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2605_12915_amd", "csrc")
 HIPCC = "/opt/rocm/bin/hipcc"
 
-# 8x8 tiles: up to 256 in FP64, up to 640 in FP32
-SIZES = [(128, 128), (129, 128), (150, 150), (151, 149), (16, 1030), (2061, 13), (165, 100), (200, 205), (208, 200)]
+# 8x8 tiles: up to 256 in FP64, up to 640 in FP32; in FP32 1024 threads up to 256 tiles of 31x10
+SIZES = [(128, 128), (129, 128), (150, 150), (151, 149), (16, 1030), (2061, 13), (165, 100), (200, 205), (208, 200),
+         (248, 320), (249, 320), (125, 511)]
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc missing")
