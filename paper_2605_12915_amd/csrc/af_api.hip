@@ -171,7 +171,8 @@ af_status status_from_bits(unsigned b) {
     return AF_OK;
 }
 
-hipError_t launch_step(af_ctx* c, void* const in[16], void* const out[16], double dt, bool timed, int word = 0) {
+hipError_t launch_step(af_ctx* c, void* const in[16], void* const out[16], double dt, bool timed, int word = 0,
+                       bool fresh = false) {
     af::StepArgs a;
     a.nx = c->cfg.nx;
     a.ny = c->cfg.ny;
@@ -188,6 +189,7 @@ hipError_t launch_step(af_ctx* c, void* const in[16], void* const out[16], doubl
     a.variant = c->variant;
     for (int k = 0; k < 4; ++k) a.bg[k] = c->cfg.bg[k];
     a.comp = c->comp;
+    a.fresh = fresh;
     if (c->f32) return af::launch_step_fused_f32(a);
     if (c->variant == 3) return af::launch_step_fc_f64(a);
     if (c->variant == 1) return af::launch_step_multi_f64(a);
@@ -201,13 +203,26 @@ hipError_t copy_state(af_ctx* c, void* const dst[16], void* const src[16]) {
 
 // AF_F32: the Kahan compensation belongs to one trajectory.  A call continues it only
 // when its input is the buffer that holds the previous call's output; any other input
-// (including the previous input again) starts a new trajectory with zeroed compensation.
-hipError_t follow_trajectory(af_ctx* c, const void* in, const void* out) {
+// (including the previous input again) starts a new trajectory with zero compensation.
+// *fresh: the call's first step starts one; it writes the compensation of every cell without
+// reading any, which saves a pass that zeroes the planes and the load of the zeros (an AF_F32
+// call of 20 steps on 256^2: 5 of 237 us; 4096^2, 4 steps: 35 of 6316).  With AF_CHECK the planes are
+// zeroed, since a rollback restores them.
+hipError_t follow_trajectory(af_ctx* c, const void* in, const void* out, bool* fresh) {
+    *fresh = false;
     if (!c->f32) return hipSuccess;
     const bool same = in == c->traj_out;
     c->traj_out = out;
     if (same) return hipSuccess;
-    return af::launch_zero(c->comp, 4 * c->N * sizeof(float), c->stream);
+    if (c->cfg.flags & AF_CHECK) return af::launch_zero(c->comp, 4 * c->N * sizeof(float), c->stream);
+    *fresh = true;
+    return hipSuccess;
+}
+
+// A step that was not launched leaves no trajectory to continue.
+hipError_t launched(af_ctx* c, hipError_t e) {
+    if (e != hipSuccess) c->traj_out = nullptr;
+    return e;
 }
 
 // AF_CHECK rollback buffer: 16 state planes plus, for AF_F32, the 4 compensation planes.
@@ -544,13 +559,14 @@ af_status af_step_out(af_ctx* c, const af_state* in, af_state* out, double dt) {
     planes_of(in, pi);
     planes_of(out, po);
     const bool check = (c->cfg.flags & AF_CHECK) != 0;
-    AF_HIP(follow_trajectory(c, pi[0], po[0]));
+    bool fresh;
+    AF_HIP(follow_trajectory(c, pi[0], po[0], &fresh));
     // AF_CHECK on an AF_F32 context: keep the compensation for a rollback
     if (check && c->f32) {
         AF_HIP(ensure_snap(c));
         AF_HIP(hipMemcpyAsync(snap_comp(c), c->comp, 4 * c->N * sizeof(float), hipMemcpyDeviceToDevice, c->stream));
     }
-    AF_HIP(launch_step(c, pi, po, dt, false));
+    AF_HIP(launched(c, launch_step(c, pi, po, dt, false, 0, fresh)));
     if (check) {
         unsigned bits;
         af_status s = read_status(c, &bits);
@@ -572,7 +588,8 @@ af_status af_step(af_ctx* c, af_state* inout, double dt, int32_t nsteps) {
     planes_of(inout, a);
     planes_of_buffer(c->state2, c->N, c->elem, b);
     // the result ends in *inout: it is the buffer that continues the trajectory
-    AF_HIP(follow_trajectory(c, a[0], a[0]));
+    bool fresh;
+    AF_HIP(follow_trajectory(c, a[0], a[0], &fresh));
     const bool check = (c->cfg.flags & AF_CHECK) != 0;
     void* snap[16] = {};
     if (check) {
@@ -588,7 +605,7 @@ af_status af_step(af_ctx* c, af_state* inout, double dt, int32_t nsteps) {
         void** src = (s & 1) ? b : a;
         void** dst = (s & 1) ? a : b;
         const int word = check ? s % kCheckSteps : 0;
-        AF_HIP(launch_step(c, src, dst, dt, false, word));
+        AF_HIP(launched(c, launch_step(c, src, dst, dt, false, word, fresh && s == 0)));
         if (check && (word == kCheckSteps - 1 || s == nsteps - 1)) {
             unsigned bits;
             af_status st = read_status(c, &bits, word + 1);

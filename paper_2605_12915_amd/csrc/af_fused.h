@@ -34,10 +34,11 @@ __device__ __forceinline__ void store_prim(const SP& o, size_t g, const Prim<T>&
 // feet at a common offset).  DYN: the family of a target is a run-time value, so a
 // wavefront holding targets of two families runs one instruction stream instead of
 // both families' code one after the other.
+// fresh (KAHAN): the step starts a trajectory, whatever comp holds is not read.
 template <int NT, int SCHEME, bool KAHAN, int RW = 0, bool DYN = false, class Tile, class Pol, class SP,
           class T = typename Tile::S>
 __device__ __forceinline__ void fused_tile(Tile& L, const SP& in, const SP& out, T* comp, int nx, int ny, int i0,
-                                           int j0, const Pol pol, T lam0, T lam1, unsigned& st) {
+                                           int j0, const Pol pol, T lam0, T lam1, unsigned& st, bool fresh = false) {
     constexpr int TX = Tile::X, TY = Tile::Y;
     const int tid = threadIdx.x;
 
@@ -201,7 +202,7 @@ __device__ __forceinline__ void fused_tile(Tile& L, const SP& in, const SP& out,
                     const size_t N = (size_t)nx * ny;
                     auto* __restrict__ cg = (__attribute__((address_space(1))) T*)comp;
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) oldc[r][k] = cg[k * N + g];
+                    for (int k = 0; k < 4; ++k) oldc[r][k] = fresh ? T(0) : cg[k * N + g];
                 }
             }
         }
@@ -273,7 +274,7 @@ __device__ __forceinline__ void fused_tile(Tile& L, const SP& in, const SP& out,
                     const size_t N = (size_t)nx * ny;
                     auto* __restrict__ cg = (__attribute__((address_space(1))) T*)comp;
                     const T old = in.p[k][g];
-                    const T y_ = delta - cg[k * N + g];
+                    const T y_ = delta - (fresh ? T(0) : cg[k * N + g]);
                     const T t_ = old + y_;
                     cg[k * N + g] = (t_ - old) - y_;
                     out.p[k][g] = t_;
@@ -294,7 +295,8 @@ using StepTile = std::conditional_t<PACK, PackedTile<T, TX, TY>, FusedTile<T, TX
 template <class T, class Pol, int TX, int TY, int NT, int SCHEME, bool KAHAN, int MINW = 1, int RW = 0,
           bool DYN = false, bool PACK = false>
 __global__ void __launch_bounds__(NT, MINW) k_fused(StatePtrs<T> in, StatePtrs<T> out, T* comp, int nx, int ny,
-                                              int tiles_x, int ntiles, Pol pol, T lam0, T lam1, unsigned* status) {
+                                              int tiles_x, int ntiles, Pol pol, T lam0, T lam1, unsigned* status,
+                                              bool fresh) {
     extern __shared__ __align__(16) unsigned char smem[];
     auto& L = *reinterpret_cast<StepTile<T, TX, TY, PACK>*>(smem);
     // XCD-aware numbering: hardware dispatches consecutive workgroups round-robin over
@@ -308,7 +310,7 @@ __global__ void __launch_bounds__(NT, MINW) k_fused(StatePtrs<T> in, StatePtrs<T
     }
     unsigned st = 0;
     fused_tile<NT, SCHEME, KAHAN, RW, DYN>(L, in, out, comp, nx, ny, (tile % tiles_x) * TX, (tile / tiles_x) * TY, pol,
-                                           lam0, lam1, st);
+                                           lam0, lam1, st, fresh);
     if (st) atomicOr(status, st);
 }
 
@@ -326,10 +328,10 @@ hipError_t launch_fused(const StepArgs& a, const Pol& pol) {
     if (a.ev_begin) (void)hipEventRecord(a.ev_begin, a.stream);
     if (a.scheme == 0)
         hipLaunchKernelGGL((k_fused<T, Pol, TX, TY, NT, 0, KAHAN, MINW, RW, DYN, PACK>), dim3(ntiles), dim3(NT), lds, a.stream, in, out, comp,
-                           a.nx, a.ny, tiles_x, ntiles, pol, lam0, lam1, a.status);
+                           a.nx, a.ny, tiles_x, ntiles, pol, lam0, lam1, a.status, a.fresh);
     else
         hipLaunchKernelGGL((k_fused<T, Pol, TX, TY, NT, 1, KAHAN, MINW, RW, DYN, PACK>), dim3(ntiles), dim3(NT), lds, a.stream, in, out, comp,
-                           a.nx, a.ny, tiles_x, ntiles, pol, lam0, lam1, a.status);
+                           a.nx, a.ny, tiles_x, ntiles, pol, lam0, lam1, a.status, a.fresh);
     if (a.ev_end) (void)hipEventRecord(a.ev_end, a.stream);
     return hipGetLastError();
 }

@@ -25,6 +25,7 @@ struct StepArgs {
     int variant;                // kernel variant (path-specific)
     double bg[4];               // FP32 path: background (rho, u, v, p) of the perturbations
     void* comp;                 // FP32 path: 4 compensation planes of the average update
+    bool fresh;                 // FP32 path: the step starts a trajectory and does not read comp
 };
 
 // Diagnostics partials: 11 values per block (5 sums, min rho, min p, max(|u|+c),

@@ -58,3 +58,30 @@ def test_step_vs_oracle(orc, nx, ny, scheme):
     err = np.abs(from_perturbation(x.cpu().numpy(), P.bg, P.gamma) - want).max(axis=(1, 2))
     tol = f32_tolerance(want, s0, P.bg, P.gamma, n)
     assert np.all(err <= tol), (st.dominant_kernel(), err / tol)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nx,ny", [(24, 17), (208, 200), (300, 301)])   # one of each FP32 kernel
+def test_f32_new_trajectory(nx, ny):
+    """A call on another buffer reads nothing of the compensation that an earlier trajectory
+    left: bit for bit the result of a new context, checked steps too."""
+    import torch
+
+    from paper_2605_12915_amd.stepper import Stepper, to_perturbation
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    dev = torch.device("cuda:0")
+    P = I.random_smooth(nx, ny, seed=nx, amp=0.1, vel=(0.35, -0.25))
+    s0, dt = to_perturbation(P.state(), P.bg, P.gamma), P.dt_for_cfl(0.4)
+    got = []
+    for used, check in ((False, False), (True, False), (True, True)):
+        st = Stepper(nx, ny, P.h, P.gamma, precision="f32", bg=P.bg, device=dev, check_errors=check)
+        if used:
+            y = torch.from_numpy(s0).to(dev)
+            st.step(y, dt, 3)
+        x, z = torch.from_numpy(s0).to(dev), torch.empty(16, ny, nx, dtype=torch.float32, device=dev)
+        st.step(x, dt, 3)
+        st.step_out(x, dt, z)
+        got.append((x.cpu(), z.cpu()))
+    for x, z in got[1:]:
+        assert torch.equal(x, got[0][0]) and torch.equal(z, got[0][1])
