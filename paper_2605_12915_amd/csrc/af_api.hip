@@ -985,6 +985,10 @@ const char* af_dominant_kernel(af_ctx* c) {
     }
     const bool rb = c && (c->cfg.flags & AF_SCHEME_RB);
     const bool small = c && af::small_grid(c->f32, c->cfg.nx, c->cfg.ny);
+    const bool tiny = c && af::tiny_grid(c->cfg.nx, c->cfg.ny);
+    if (c && c->f32 && tiny)
+        return rb ? "af::k_fused<float, af::PolPert<float>, 4, 4, 128, 1, true, 1, 0, true, false>"
+                  : "af::k_fused<float, af::PolPert<float>, 4, 4, 128, 0, true, 1, 0, true, false>";
     if (c && c->f32 && small)
         return rb ? "af::k_fused<float, af::PolPert<float>, 8, 8, 256, 1, true, 4, 0, true, true>"
                   : "af::k_fused<float, af::PolPert<float>, 8, 8, 256, 0, true, 4, 0, true, true>";
@@ -997,6 +1001,9 @@ const char* af_dominant_kernel(af_ctx* c) {
     if (c && c->variant == 3) return "af::k_fc_points";
     if (c && c->variant == 1) return "af_step multi-kernel sequence";
     if (c && c->variant == 2) return rb ? "af::k_points_update<32, 8, 512, 1>" : "af::k_points_update<32, 8, 512, 0>";
+    if (tiny)
+        return rb ? "af::k_fused<double, af::PolAbs<double>, 4, 4, 128, 1, false, 1, 0, true, false>"
+                  : "af::k_fused<double, af::PolAbs<double>, 4, 4, 128, 0, false, 1, 0, true, false>";
     if (small)
         return rb ? "af::k_fused<double, af::PolAbs<double>, 8, 8, 256, 1, false, 1, 0, true, true>"
                   : "af::k_fused<double, af::PolAbs<double>, 8, 8, 256, 0, false, 1, 0, true, true>";

@@ -43,15 +43,24 @@ constexpr int kTX = 15, kTY = 10, kNT = 512, kRW = 16, kMinW = 4;
 // and 8x8 tiles: 64^2 9.8 and 7.9, 96^2 10.0 and 8.2, 128^2 (256 tiles) 10.4 and 8.6; beyond, at
 // 192^2, 14.9 and 16.0).
 constexpr int kSX = 8, kSY = 8, kSNT = 256;
+// And grids of at most one 4x4 tile per CU spread over four times the CUs, two wavefronts to a
+// tile (unpacked: packing buys nothing at 22 KB of LDS).  us per step with 8x8 and 4x4 tiles:
+// 32^2 7.8 and 7.0, 64^2 (256 tiles) 7.9 and 7.2; at 72^2 (324 tiles) 8.1 and 9.2.  With two
+// lanes to a target, one for each duration, 64^2 took 8.0.
+constexpr int kTinyX = 4, kTinyY = 4, kTinyNT = 128;
 
 hipError_t launch_step_fused_f64(const StepArgs& a) {
     PolAbs<double> pol{a.gamma, 1.0 / (a.gamma - 1.0)};
+    if (tiny_grid(a.nx, a.ny))
+        return launch_fused<double, PolAbs<double>, kTinyX, kTinyY, kTinyNT, false, 1, 0, true, false>(a, pol);
     if (small_grid(false, a.nx, a.ny))
         return launch_fused<double, PolAbs<double>, kSX, kSY, kSNT, false, 1, 0, true, true>(a, pol);
     return launch_fused<double, PolAbs<double>, kTX, kTY, kNT, false, kMinW, kRW, true, true>(a, pol);
 }
 
 hipError_t prepare_fused_f64(int nx, int ny) {
+    if (tiny_grid(nx, ny))
+        return prepare_fused<double, PolAbs<double>, kTinyX, kTinyY, kTinyNT, false, 1, 0, true, false>();
     if (small_grid(false, nx, ny)) return prepare_fused<double, PolAbs<double>, kSX, kSY, kSNT, false, 1, 0, true, true>();
     return prepare_fused<double, PolAbs<double>, kTX, kTY, kNT, false, kMinW, kRW, true, true>();
 }

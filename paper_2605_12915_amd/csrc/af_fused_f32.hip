@@ -49,7 +49,7 @@ hipError_t launch_step_fused_f32(const StepArgs& a) {
 }
 
 hipError_t prepare_fused_f32(int nx, int ny) {
-    if (small_grid(true, nx, ny)) return prepare_fused_f32_small();
+    if (small_grid(true, nx, ny)) return prepare_fused_f32_small(nx, ny);
     if (one_tile_per_cu_f32(nx, ny))
         return prepare_fused<float, PolPert<float>, kFTX, kFTY, kFNTWide, true, kFMinW, kFRW, true>();
     return prepare_fused<float, PolPert<float>, kFTX, kFTY, kFNT, true, kFMinW, kFRW, true>();

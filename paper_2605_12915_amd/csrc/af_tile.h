@@ -112,6 +112,7 @@ struct PackedTile {
             T GE[4][VY][TX];
         } F;
     };
+    static_assert(DX >= W && CX >= W, "regions hold the walk's W columns");
     static_assert(4 * PX <= CY * 4 * SC, "the Ev row without a place falls on the centres");
     // planes of a row: V, Eh, Ev; increments V, Eh, Ev, C (each family's durations together)
     static AF_HD constexpr int slot(int fam) { return fam == F_EH ? 1 : (fam == F_EV ? 2 : fam); }

@@ -53,10 +53,13 @@ KERNEL_SOURCES = {
        ["csrc/af_fused.hip"] + _STEP for s in (0, 1)},
     **{f"af::k_fused<double, af::PolAbs<double>, 8, 8, 256, {s}, false, 1, 0, true, true>":
        ["csrc/af_fused.hip"] + _STEP for s in (0, 1)},
+    **{f"af::k_fused<double, af::PolAbs<double>, 4, 4, 128, {s}, false, 1, 0, true, false>":
+       ["csrc/af_fused.hip"] + _STEP for s in (0, 1)},
     **{f"af::k_fused<float, af::PolPert<float>, 31, 10, {nt}, 0, true, 4, 32, true, false>":
        ["csrc/af_fused_f32.hip"] + _STEP for nt in (512, 1024)},
-    "af::k_fused<float, af::PolPert<float>, 8, 8, 256, 0, true, 4, 0, true, true>":
-        ["csrc/af_fused_f32_small.hip", "csrc/af_fused_f32.hip"] + _STEP,
+    **{f"af::k_fused<float, af::PolPert<float>, {t}>":
+       ["csrc/af_fused_f32_small.hip", "csrc/af_fused_f32.hip"] + _STEP
+       for t in ("8, 8, 256, 0, true, 4, 0, true, true", "4, 4, 128, 0, true, 1, 0, true, false")},
     "af::k_fused_batch_direct<31, 10, 512, 4, 0, 32>": ["csrc/af_batch.hip", "csrc/af_batch.h"] + _STEP,
     **{k: _ADJ for k in ADJOINT_KERNELS},
     "af::k_fc_points": ["csrc/af_f64.hip", "csrc/af_footcentred.h", "csrc/af_gauss.h", "csrc/af_kernels.h",

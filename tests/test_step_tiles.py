@@ -15,8 +15,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2605_12915_amd", "csrc")
 HIPCC = "/opt/rocm/bin/hipcc"
 
-# 8x8 tiles: up to 256 in FP64, up to 640 in FP32; in FP32 1024 threads up to 256 tiles of 31x10
-SIZES = [(128, 128), (129, 128), (150, 150), (151, 149), (16, 1030), (2061, 13), (165, 100), (200, 205), (208, 200),
+# 4x4 tiles: up to 256; 8x8 tiles: up to 256 in FP64, up to 640 in FP32; in FP32 1024 threads up to 256 tiles of 31x10
+SIZES = [(64, 64), (65, 64), (4, 4), (5, 203), (128, 128), (129, 128), (150, 150), (151, 149), (16, 1030), (2061, 13), (165, 100), (200, 205), (208, 200),
          (248, 320), (249, 320), (125, 511)]
 
 
@@ -61,7 +61,7 @@ def test_step_vs_oracle(orc, nx, ny, scheme):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("nx,ny", [(24, 17), (208, 200), (300, 301)])   # one of each FP32 kernel
+@pytest.mark.parametrize("nx,ny", [(24, 17), (77, 65), (208, 200), (300, 301)])   # one of each FP32 kernel
 def test_f32_new_trajectory(nx, ny):
     """A call on another buffer reads nothing of the compensation that an earlier trajectory
     left: bit for bit the result of a new context, checked steps too."""
