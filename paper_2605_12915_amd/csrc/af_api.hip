@@ -467,8 +467,11 @@ const char* af_status_string(af_status s) {
 int32_t af_last_hip_error(void) { return g_last_hip; }
 
 // Largest grid a context accepts: 2^31 cells (275 GB of FP64 state, more than one GPU
-// holds with a second state), which keeps every byte count in size_t and every launch
-// within HIP's 2^32 work-items per grid dimension.
+// holds with a second state), which keeps every byte count in size_t and every tile number
+// in int.  The step kernels split the tiles over launches within HIP's 2^32 work-items per axis
+// (tile_runs), the foot-centred update its cells; the adjoint, with 120 planes of doubles in
+// all, ends at 3e8 cells and at most 8 work-items to a cell.  (A batch's step is one launch:
+// one of grids four cells wide, 16 work-items to a cell, ends at 2.7e8 cells.)
 constexpr uint64_t kMaxCells = uint64_t(1) << 31;
 
 af_status af_init(const af_config* cfg, void* hip_stream, af_ctx** out) {

@@ -295,16 +295,16 @@ using StepTile = std::conditional_t<PACK, PackedTile<T, TX, TY>, FusedTile<T, TX
 template <class T, class Pol, int TX, int TY, int NT, int SCHEME, bool KAHAN, int MINW = 1, int RW = 0,
           bool DYN = false, bool PACK = false>
 __global__ void __launch_bounds__(NT, MINW) k_fused(StatePtrs<T> in, StatePtrs<T> out, T* comp, int nx, int ny,
-                                              int tiles_x, int ntiles, Pol pol, T lam0, T lam1, unsigned* status,
-                                              bool fresh) {
+                                              int tiles_x, int tile0, int ntiles, Pol pol, T lam0, T lam1,
+                                              unsigned* status, bool fresh) {
     extern __shared__ __align__(16) unsigned char smem[];
     auto& L = *reinterpret_cast<StepTile<T, TX, TY, PACK>*>(smem);
     // XCD-aware numbering: hardware dispatches consecutive workgroups round-robin over
-    // the 8 XCDs; give each XCD a contiguous run of tiles.
+    // the 8 XCDs; give each XCD a contiguous run of the launch's tiles [tile0, tile0 + ntiles).
     int tile;
     {
         const int b = blockIdx.x, xcd = b & 7;
-        int base = 0;
+        int base = tile0;
         for (int x = 0; x < xcd; ++x) base += (ntiles - x + 7) >> 3;
         tile = base + (b >> 3);
     }
@@ -326,12 +326,16 @@ hipError_t launch_fused(const StepArgs& a, const Pol& pol) {
     const size_t lds = sizeof(StepTile<T, TX, TY, PACK>);
     T* comp = (T*)a.comp;
     if (a.ev_begin) (void)hipEventRecord(a.ev_begin, a.stream);
-    if (a.scheme == 0)
-        hipLaunchKernelGGL((k_fused<T, Pol, TX, TY, NT, 0, KAHAN, MINW, RW, DYN, PACK>), dim3(ntiles), dim3(NT), lds, a.stream, in, out, comp,
-                           a.nx, a.ny, tiles_x, ntiles, pol, lam0, lam1, a.status, a.fresh);
-    else
-        hipLaunchKernelGGL((k_fused<T, Pol, TX, TY, NT, 1, KAHAN, MINW, RW, DYN, PACK>), dim3(ntiles), dim3(NT), lds, a.stream, in, out, comp,
-                           a.nx, a.ny, tiles_x, ntiles, pol, lam0, lam1, a.status, a.fresh);
+    tile_runs<NT>(ntiles, [&](int tile0, int count) {
+        if (a.scheme == 0)
+            hipLaunchKernelGGL((k_fused<T, Pol, TX, TY, NT, 0, KAHAN, MINW, RW, DYN, PACK>), dim3(count), dim3(NT), lds,
+                               a.stream, in, out, comp, a.nx, a.ny, tiles_x, tile0, count, pol, lam0, lam1, a.status,
+                               a.fresh);
+        else
+            hipLaunchKernelGGL((k_fused<T, Pol, TX, TY, NT, 1, KAHAN, MINW, RW, DYN, PACK>), dim3(count), dim3(NT), lds,
+                               a.stream, in, out, comp, a.nx, a.ny, tiles_x, tile0, count, pol, lam0, lam1, a.status,
+                               a.fresh);
+    });
     if (a.ev_end) (void)hipEventRecord(a.ev_end, a.stream);
     return hipGetLastError();
 }

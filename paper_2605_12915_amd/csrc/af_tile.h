@@ -179,6 +179,16 @@ using LdsAcc = TileAcc<FusedTile<T, TX, TY>>;
 template <class T, int TX, int TY>
 using LdsInc = TileInc<FusedTile<T, TX, TY>>;
 
+// The launches that take a grid's ntiles tiles, a workgroup of NT threads to each:
+// launch(first tile, number).  HIP takes fewer than 2^32 work-items along an axis of a
+// launch, and a grid of 2^31 cells has up to 2^31 / 40 tiles of 15 x 10 (four columns), 2.7e10
+// work-items; at most 2^31 of them to a launch.
+template <int NT, class F>
+void tile_runs(int ntiles, const F& launch) {
+    constexpr int most = (1 << 30) / NT * 2;
+    for (int t = 0; t < ntiles; t += most) launch(t, ntiles - t < most ? ntiles - t : most);
+}
+
 AF_HD int wrap_any(int v, int n) {
     v %= n;
     return v < 0 ? v + n : v;
