@@ -65,9 +65,11 @@ struct DiagAcc {
     }
 };
 
-// Two waves per SIMD (181 registers, no spill).  With the logarithm of af_math.h the
+// Two waves per SIMD (195 registers, no spill).  With the logarithm of af_math.h the
 // 4-wave cap that suited the library's logarithm (5 dwords spilled then, 0.29 ms per call
 // at 2048^2) spills 56 dwords (0.73 ms) and a 3-wave cap 14 (0.30 ms); 0.23 ms here.
+// The sums' rounding errors (diag_add) cost 14 registers and 2-4% of a call: 64x32 33 us with
+// and without, 1000^2 72 and 74, 2048^2 189 and 195, 4096^2 662 and 687 (a uniform state).
 template <class T>
 __global__ void __launch_bounds__(kDiagBlock, 2) k_diag(StatePtrs<const T> st, int nx, int ny, double gamma,
                                                      DiagBg bgs, double* partials) {
@@ -82,6 +84,7 @@ __global__ void __launch_bounds__(kDiagBlock, 2) k_diag(StatePtrs<const T> st, i
     for (int k = 0; k < 16; ++k) A.s[k] = st.p[k];
     double v[kDiagVals];
     diag_init(v);
+    DiagLo lo{};
     const size_t N = (size_t)nx * ny;
     // Entropy: the tensor Simpson rule over the nine Q2 nodes of every cell, summed
     // over cells, gives each node the sum of its weights in the cells that share it:
@@ -100,18 +103,22 @@ __global__ void __launch_bounds__(kDiagBlock, 2) k_diag(StatePtrs<const T> st, i
             i = (int)(c % nx);
             j = (int)(c / nx);
         }
+        double d[kDiagVals];
+        diag_init(d);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] += A.val(k, c);
+        for (int k = 0; k < 4; ++k) d[k] = A.val(k, c);
         const Prim<double> own[4] = {A.point(F_V, i, j), A.point(F_EV, i, j), A.point(F_EH, i, j), A.node(F_C, i, j)};
 #pragma unroll
-        for (int f = 0; f < 4; ++f) diag_node(v, wnode[f], own[f].r, own[f].u, own[f].v, own[f].p, gamma);
+        for (int f = 0; f < 4; ++f) diag_node(d, wnode[f], own[f].r, own[f].u, own[f].v, own[f].p, gamma);
         // the cell's nine velocity nodes, [x-node][y-node]
         const Prim<double> v10 = A.point(F_V, i + 1, j), v01 = A.point(F_V, i, j + 1), v11 = A.point(F_V, i + 1, j + 1);
         const Prim<double> ev1 = A.point(F_EV, i + 1, j), eh1 = A.point(F_EH, i, j + 1);
         const double cu[3][3] = {{own[0].u, own[1].u, v01.u}, {own[2].u, own[3].u, eh1.u}, {v10.u, ev1.u, v11.u}};
         const double cv[3][3] = {{own[0].v, own[1].v, v01.v}, {own[2].v, own[3].v, eh1.v}, {v10.v, ev1.v, v11.v}};
-        diag_vorticity(v, cu, cv);
+        diag_vorticity(d, cu, cv);
+        diag_add(v, lo, d);
     }
+    diag_close(v, lo);
     block_reduce(v, sh);
     if (threadIdx.x == 0)
         for (int k = 0; k < kDiagVals; ++k) partials[(size_t)blockIdx.x * kDiagVals + k] = v[k];

