@@ -608,10 +608,13 @@ af_status af_step(af_ctx* c, af_state* inout, double dt, int32_t nsteps) {
         void** src = (s & 1) ? b : a;
         void** dst = (s & 1) ? a : b;
         const int word = check ? s % kCheckSteps : 0;
-        AF_HIP(launched(c, launch_step(c, src, dst, dt, false, word, fresh && s == 0)));
-        if (check && (word == kCheckSteps - 1 || s == nsteps - 1)) {
+        const hipError_t e = launched(c, launch_step(c, src, dst, dt, false, word, fresh && s == 0));
+        // (a step that was not launched ends the call: the words of those before it are read
+        // first, so that their status is this call's and none is left for the next)
+        const int words = e == hipSuccess ? word + 1 : word;
+        if (check && words > 0 && (words == kCheckSteps || s == nsteps - 1 || e != hipSuccess)) {
             unsigned bits;
-            af_status st = read_status(c, &bits, word + 1);
+            af_status st = read_status(c, &bits, words);
             if (st != AF_OK) return st;
             if (bits) {
                 // *inout returns to the input of the call (a single step writes the partner
@@ -624,6 +627,7 @@ af_status af_step(af_ctx* c, af_state* inout, double dt, int32_t nsteps) {
                 return status_from_bits(bits);
             }
         }
+        AF_HIP(e);
     }
     if (nsteps & 1) AF_HIP(copy_state(c, a, b));
     return AF_OK;
