@@ -1008,6 +1008,9 @@ const char* af_dominant_kernel(af_ctx* c) {
     if (c && c->variant == 3) return "af::k_fc_points";
     if (c && c->variant == 1) return "af_step multi-kernel sequence";
     if (c && c->variant == 2) return rb ? "af::k_points_update<32, 8, 512, 1>" : "af::k_points_update<32, 8, 512, 0>";
+    if (c && af::wide_grid(c->cfg.nx, c->cfg.ny))
+        return rb ? "af::k_fused<double, af::PolAbs<double>, 31, 10, 512, 1, false, 1, 32, true, false>"
+                  : "af::k_fused<double, af::PolAbs<double>, 31, 10, 512, 0, false, 1, 32, true, false>";
     if (tiny)
         return rb ? "af::k_fused<double, af::PolAbs<double>, 4, 4, 128, 1, false, 1, 0, true, false>"
                   : "af::k_fused<double, af::PolAbs<double>, 4, 4, 128, 0, false, 1, 0, true, false>";

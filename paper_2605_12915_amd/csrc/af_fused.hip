@@ -49,8 +49,18 @@ constexpr int kSX = 8, kSY = 8, kSNT = 256;
 // lanes to a target, one for each duration, 64^2 took 8.0.
 constexpr int kTinyX = 4, kTinyY = 4, kTinyNT = 128;
 
+// Grids whose 15x10 tiles just exceed the 512 that run at once, so that a few tiles make a
+// second round, while 31x10 tiles fit the CUs in one (wide_grid): 256 registers, one workgroup
+// to a CU.  us per step with 15x10 and 31x10 tiles: 31x1701 20.9 and 16.1, 61x1100 20.6 and 15.6; in two
+// rounds of wide tiles the narrow ones are the faster (62x2000 26.5 and 28.4) but for 31 columns,
+// which take three of them to a wide one (31x4096 32.5 and 29.0, 31x30000 191 and 160; 31x2570,
+// 257 wide tiles, 26.9 and 28.2).
+constexpr int kWX = 31, kWY = 10, kWNT = 512, kWRW = 32;
+
 hipError_t launch_step_fused_f64(const StepArgs& a) {
     PolAbs<double> pol{a.gamma, 1.0 / (a.gamma - 1.0)};
+    if (wide_grid(a.nx, a.ny))
+        return launch_fused<double, PolAbs<double>, kWX, kWY, kWNT, false, 1, kWRW, true, false>(a, pol);
     if (tiny_grid(a.nx, a.ny))
         return launch_fused<double, PolAbs<double>, kTinyX, kTinyY, kTinyNT, false, 1, 0, true, false>(a, pol);
     if (small_grid(false, a.nx, a.ny))
@@ -59,6 +69,7 @@ hipError_t launch_step_fused_f64(const StepArgs& a) {
 }
 
 hipError_t prepare_fused_f64(int nx, int ny) {
+    if (wide_grid(nx, ny)) return prepare_fused<double, PolAbs<double>, kWX, kWY, kWNT, false, 1, kWRW, true, false>();
     if (tiny_grid(nx, ny))
         return prepare_fused<double, PolAbs<double>, kTinyX, kTinyY, kTinyNT, false, 1, 0, true, false>();
     if (small_grid(false, nx, ny)) return prepare_fused<double, PolAbs<double>, kSX, kSY, kSNT, false, 1, 0, true, true>();

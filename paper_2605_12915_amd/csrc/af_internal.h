@@ -67,6 +67,13 @@ inline bool small_grid(bool f32, int nx, int ny) {
 inline bool tiny_grid(int nx, int ny) { return ((nx + 3LL) / 4) * ((ny + 3LL) / 4) <= 256; }
 // FP32 grids of at most one 31x10 tile per CU.
 inline bool one_tile_per_cu_f32(int nx, int ny) { return ((nx + 30LL) / 31) * ((ny + 9LL) / 10) <= 256; }
+// FP64 grids of 31x10 tiles (one to a CU): those whose 15x10 tiles do not all run at once (two to
+// a CU) while the wide ones do, and beyond one and a half rounds of wide tiles those (31 columns)
+// that take three narrow tiles for each; both sides are measured at the kernel.
+inline bool wide_grid(int nx, int ny) {
+    const long long rows = (ny + 9LL) / 10, narrow = (nx + 14LL) / 15 * rows, wide = (nx + 30LL) / 31 * rows;
+    return (narrow > 512 && wide <= 256) || (narrow >= 3 * wide && wide > 384);
+}
 hipError_t prepare_fused_f64(int nx, int ny);
 hipError_t prepare_adjoint_f64();
 hipError_t launch_step_split_f64(const StepArgs& a);

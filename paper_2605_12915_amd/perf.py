@@ -51,6 +51,8 @@ KERNEL_SOURCES = {
     # the step kernels of both point updates (0: transported, 1: additive)
     **{f"af::k_fused<double, af::PolAbs<double>, 15, 10, 512, {s}, false, 4, 16, true, true>":
        ["csrc/af_fused.hip"] + _STEP for s in (0, 1)},
+    **{f"af::k_fused<double, af::PolAbs<double>, 31, 10, 512, {s}, false, 1, 32, true, false>":
+       ["csrc/af_fused.hip"] + _STEP for s in (0, 1)},
     **{f"af::k_fused<double, af::PolAbs<double>, 8, 8, 256, {s}, false, 1, 0, true, true>":
        ["csrc/af_fused.hip"] + _STEP for s in (0, 1)},
     **{f"af::k_fused<double, af::PolAbs<double>, 4, 4, 128, {s}, false, 1, 0, true, false>":

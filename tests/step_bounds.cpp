@@ -143,6 +143,7 @@ int main() {
     for (const auto& g : grids)
         for (double vmax : {0.4, 1.5}) {
             both<PackedTile<double, 15, 10>, 16, 512>(g[0], g[1], vmax, seed);
+            both<FusedTile<double, 31, 10>, 32, 512>(g[0], g[1], vmax, seed);
             both<PackedTile<double, 8, 8>, 0, 256>(g[0], g[1], vmax, seed);
             both<FusedTile<double, 4, 4>, 0, 128>(g[0], g[1], vmax, seed);
             both<PackedTile<float, 8, 8>, 0, 256>(g[0], g[1], vmax, seed);
