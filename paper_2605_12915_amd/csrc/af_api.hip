@@ -68,7 +68,7 @@ namespace {
 
 thread_local int g_last_hip = 0;
 
-constexpr int kDiagPartials = 4096;   // blocks of the first reduction pass
+constexpr int kDiagPartials = 512;   // blocks of the diagnostics' first reduction pass
 // AF_CHECK: steps whose status words are read back together.  Every step has a word of its
 // own, so the first step that failed and its status are the same as with a read-back (a
 // copy and a host synchronisation, ~15 us) after each; a failure costs the steps enqueued

@@ -15,8 +15,6 @@
 namespace af {
 
 constexpr int kDiagBlock = 256;
-constexpr int kDiagGrid = 512;
-
 
 __device__ __forceinline__ void block_reduce(double v[kDiagVals], double* sh) {
     diag_wave_reduce(v);
@@ -155,12 +153,11 @@ hipError_t launch_diag_final(const double* partials, int n, double* out9, hipStr
 hipError_t launch_diag(const void* const s[16], bool f32, const double bg[4], int nx, int ny, double h,
                        double gamma, double* partials, int npartials, double* out9, hipStream_t stream) {
     const DiagBg b = diag_bg(f32, bg, gamma);
-    // a block per 256 cells up to the two blocks a CU runs at once: more only add to the
-    // partials that one block then reduces (per call with its read-back: 64^2 61 us with 4096
-    // blocks, 33 with 16; 1000^2 93 and 77, 2048^2 245 and 229)
+    // a block per 256 cells up to npartials, the two blocks a CU runs at once: more only add to
+    // the partials that one block then reduces (per call with its read-back: 64^2 61 us with
+    // 4096 blocks, 33 with 16; 1000^2 93 and 77 with 512, 2048^2 245 and 229)
     const size_t want = ((size_t)nx * ny + kDiagBlock - 1) / kDiagBlock;
     if (want < (size_t)npartials) npartials = (int)want;
-    if (npartials > kDiagGrid) npartials = kDiagGrid;
     if (f32) {
         StatePtrs<const float> st;
         for (int k = 0; k < 16; ++k) st.p[k] = (const float*)s[k];
