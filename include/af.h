@@ -60,7 +60,7 @@ enum {
                            state taken at the convective foot and the exact solution of the
                            frozen acoustic system evaluated there by quadrature of spherical
                            means; density from the linear closure.  An analytical reference
-                           several hundred times the transported update's cost.  AF_F64
+                           160 times the transported update's cost (256^2).  AF_F64
                            single-grid contexts only, not with AF_SCHEME_RB; no adjoint.
                            Fails with AF_ERR_FOOTPRINT when |F - P| + c* tau / h >= 1/2 */
 };

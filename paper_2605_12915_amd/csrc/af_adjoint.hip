@@ -3,8 +3,9 @@
 // cot_n = (d step / d state_n)^T cot_np1 at fixed dt, in three kernels.  The reverse
 // of a gather stencil is a scatter: every block accumulates its scattered
 // contributions in an LDS window over its cells plus the reach of the stencil (LDS
-// FP64 atomics), then adds the window to global memory once (one global atomic per
-// window entry instead of one per contribution):
+// FP64 atomics).  The point kernel then adds its window to global memory (one global
+// atomic per entry instead of one per contribution); the increments kernel evaluates
+// the pairs that reach its block from outside too and stores the block's own cells:
 //   k_adj_fwd      forward intermediates recomputed from state_n (recovered centres
 //                  W^C, node increments of both durations); zeroes the accumulation
 //                  planes.
@@ -14,9 +15,9 @@
 //                  foot, values and foot position, the two Picard stages; RB: Q2 of W
 //                  at the foot, the target's own increments).  Scatters into cot_n
 //                  (point planes), lambda_C and lambda_D.
-//   k_adj_incr     transposed node increments (Horner in r, freezing c_K, Z_K,
-//                  transposed monomial blocks and Lagrange-to-monomial transforms of
-//                  every wedge), then the transposed centre recovery (prim(U_c),
+//   k_adj_incr     transposed node increments (Horner in r, freezing c_K, Z_K, the
+//                  folded blocks and the lines shared by a pair of families,
+//                  transposed), then the transposed centre recovery (prim(U_c),
 //                  inverse Simpson, U(W) at the eight boundary nodes); adds to the point
 //                  planes of cot_n and writes its average planes.
 // The floor() that locates a foot is piecewise constant: its derivative is zero
@@ -216,11 +217,16 @@ __global__ void __launch_bounds__(kFNT, 2) k_adj_fwd(StatePtrs<double> prim, dou
 // despite the larger window overlap, 1.89x against 1.63x).
 // The planes of a window row lie side by side: 40 x 11 doubles from row to row, 24 modulo the
 // 32 that the banks hold, so that the four rows of 8 lanes that a half-wavefront reads or
-// adds to at a common offset start in four distinct quarters of the banks.
+// adds to at a common offset start in four distinct quarters of the banks (512^2: 1.9e6 conflict
+// cycles for 3.7e6 LDS instructions, 8.2e6 with rows apart by plane; feet of different offsets,
+// the staging and the flush make the rest).
 // Bound by the LDS additions and by two wavefronts per SIMD hiding little of the FP64 chains:
 // both durations' feet in one cell share an addition per node and plane, and the velocities'
 // part of the increment planes is left to the increments' kernel (SCHEME 0; 512^2: 104.7 -> 94.0
-// us, 1000^2 461 -> 438).
+// us, 1000^2 461 -> 438).  That keeps both durations' weights (FootAdj) through the second
+// one's evaluation: 54 registers spilled for SCHEME 0 (60 bytes of scratch a lane; writes to memory
+// 0.047 -> 0.058 GB a launch at 512^2) and 28 for SCHEME 1, none and 2 without; the gain above is
+// net of it.
 template <int BX, int BY>
 struct PointBlock {
     static_assert(BX == BY, "square blocks");
@@ -304,10 +310,13 @@ hipError_t prepare_points() {
 // [0, B), and the centre recovery of cells [-1, B).  The forward nodes of that window are
 // staged in LDS, the contributions accumulated in an LDS window of the same shape, and the
 // block's own node-cells added to global memory by plain loads and stores.  Rows hold all
-// planes side by side ([y][plane][x], an odd multiple of 16 doubles), so that two rows fall on
-// different banks.  The pairs are evaluated 1.41 times per node-cell for that; adding each
-// block's overlapping window to global memory by atomics instead took 30 k of the block's 52 k
-// cycles (512^2: 68 us against 61; 1000^2 272 and 236).
+// planes side by side ([y][plane][x], an odd multiple of 16 doubles), so that two rows of 16
+// items fall on different banks, as the centres' and the last phase's nearly are; the pairs, the
+// bulk of the accesses, are walked in rows of 18, whose second row meets the first on the
+// banks in every half-wavefront (512^2: 3.5e6 conflict cycles for 1.7e6 LDS instructions).  The
+// pairs are evaluated 1.41 times per node-cell; adding each block's overlapping window to
+// global memory by atomics instead took 30 k of the block's 52 k cycles (512^2: 68 us against
+// 61; 1000^2 272 and 236).
 constexpr int kIBX = 16, kIBY = 8, kINT = 256;
 
 struct IncrWin {

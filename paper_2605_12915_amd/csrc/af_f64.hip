@@ -174,8 +174,12 @@ __global__ void __launch_bounds__(256) k_update(StatePtrs<double> in, const doub
 // blockIdx.y mod 3 and duration blockIdx.y / 3, cells c0 + [0, count).  One thread per target,
 // with the radial integrals by 10 Gauss points, took 13.8 M FP64 flops per cell (20.1 ms on
 // 256^2; 7.2 ms on 96^2, whose 55296 threads left most of the chip idle); exact radial
-// integrals and 32 lanes per target 2.8 ms and 0.46 ms.  Bound by its arithmetic; three waves per
-// SIMD (168 registers) against two: 2.81 and 2.92 ms on 256^2, four spill 145 registers.
+// integrals and 32 lanes per target 1.45 M flops per cell, 2.8 to 3.4 ms on 256^2 by the disks'
+// radius and 0.43 ms on 96^2.  Bound by vector issue (256^2: 1.46e9 instructions a launch, over 90%
+// of the busy cycles at the 4.2 cycles of an FP64 one); three waves per SIMD (168 registers)
+// against two: 2.81 and 2.92 ms on 256^2, four spill 145 registers.  The pointers of the 16
+// planes are indexed by the lane's own family and lie in scratch with 4 spilled registers,
+// 168 bytes a lane, 2.0 GB written a launch on 256^2.
 constexpr int kFcGroups = 8;
 
 __global__ void __launch_bounds__(32 * kFcGroups, 3) k_fc_points(StatePtrs<double> in, const double* C, double* half,

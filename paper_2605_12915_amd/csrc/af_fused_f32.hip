@@ -20,7 +20,8 @@ namespace af {
 // family fence (no more scratch traffic from spills) 1.826 ms and the FP64 row layout
 // of the staged arrays (bank conflicts cut eightfold) 1.742 ms, identical bits.
 // (at 4096^2 now 1.46 ms: the folded increments, the interpolation of u + du and the
-// field-by-field order of the points; VALU issue bound at 61% of its rate.)
+// field-by-field order of the points; bound by vector issue, 1.06e9 instructions a launch, 64% of
+// the busy cycles at two cycles to an instruction, and by the LDS.)
 constexpr int kFTX = 31, kFTY = 10, kFNT = 512, kFMinW = 4, kFRW = 32;
 
 // A grid of at most one such tile per CU (of 256) has no second workgroup to share a CU with:

@@ -361,7 +361,8 @@ AF_HD void point_update_pair_f(const A& acc, const D& d0, const D& d1, int fam, 
         }
         if constexpr (!SUM) {
             // the velocities gathered a second time: kept from the first stage they would
-            // exceed 128 registers in FP64
+            // exceed the 128 registers of the FP64 15x10 kernel (the FP32 additive kernels, of
+            // 119 to 128 registers, take the second gather with it)
             reload_fence();
             cell_field<1>(acc, ci, cj, g);
 #pragma unroll
