@@ -289,22 +289,27 @@ __device__ __forceinline__ void fused_tile(Tile& L, const SP& in, const SP& out,
 template <class T, int TX, int TY, bool PACK>
 using StepTile = std::conditional_t<PACK, PackedTile<T, TX, TY>, FusedTile<T, TX, TY>>;
 
+// Kernels whose grids may need more launches than one (tile_runs); the others take 640 tiles at most.
+constexpr bool many_tiles(int TX, int NT) { return TX >= 15 && NT == 512; }
+
 // ---- single-grid kernel: one tile per workgroup --------------------------------------
 // MINW: minimum wavefronts per SIMD the register allocation must allow (1: no
 // constraint beyond the workgroup size; 4 at 512 threads: two workgroups per CU).
 template <class T, class Pol, int TX, int TY, int NT, int SCHEME, bool KAHAN, int MINW = 1, int RW = 0,
           bool DYN = false, bool PACK = false>
 __global__ void __launch_bounds__(NT, MINW) k_fused(StatePtrs<T> in, StatePtrs<T> out, T* comp, int nx, int ny,
-                                              int tiles_x, int tile0, int ntiles, Pol pol, T lam0, T lam1,
-                                              unsigned* status, bool fresh) {
+                                              int tiles_x, int ntiles, Pol pol, T lam0, T lam1, unsigned* status,
+                                              bool fresh, int tile0) {
     extern __shared__ __align__(16) unsigned char smem[];
     auto& L = *reinterpret_cast<StepTile<T, TX, TY, PACK>*>(smem);
     // XCD-aware numbering: hardware dispatches consecutive workgroups round-robin over
-    // the 8 XCDs; give each XCD a contiguous run of the launch's tiles [tile0, tile0 + ntiles).
+    // the 8 XCDs; give each XCD a contiguous run of the launch's tiles [tile0, tile0 + ntiles)
+    // (the kernels of small grids do without tile0: its load and addition at the head of their
+    // short chain took up to 1% of a step).
     int tile;
     {
         const int b = blockIdx.x, xcd = b & 7;
-        int base = tile0;
+        int base = many_tiles(TX, NT) ? tile0 : 0;
         for (int x = 0; x < xcd; ++x) base += (ntiles - x + 7) >> 3;
         tile = base + (b >> 3);
     }
@@ -329,12 +334,12 @@ hipError_t launch_fused(const StepArgs& a, const Pol& pol) {
     tile_runs<NT>(ntiles, [&](int tile0, int count) {
         if (a.scheme == 0)
             hipLaunchKernelGGL((k_fused<T, Pol, TX, TY, NT, 0, KAHAN, MINW, RW, DYN, PACK>), dim3(count), dim3(NT), lds,
-                               a.stream, in, out, comp, a.nx, a.ny, tiles_x, tile0, count, pol, lam0, lam1, a.status,
-                               a.fresh);
+                               a.stream, in, out, comp, a.nx, a.ny, tiles_x, count, pol, lam0, lam1, a.status, a.fresh,
+                               tile0);
         else
             hipLaunchKernelGGL((k_fused<T, Pol, TX, TY, NT, 1, KAHAN, MINW, RW, DYN, PACK>), dim3(count), dim3(NT), lds,
-                               a.stream, in, out, comp, a.nx, a.ny, tiles_x, tile0, count, pol, lam0, lam1, a.status,
-                               a.fresh);
+                               a.stream, in, out, comp, a.nx, a.ny, tiles_x, count, pol, lam0, lam1, a.status, a.fresh,
+                               tile0);
     });
     if (a.ev_end) (void)hipEventRecord(a.ev_end, a.stream);
     return hipGetLastError();
